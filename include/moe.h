@@ -333,11 +333,11 @@ int moe_dispatch_ex(const void* x, const float* x_scales, int dtype, int64_t T, 
  * expert_y  [R] uint64 bf16 region bases (device table), 16-byte aligned.
  * topk_w    [T,k] float32.
  * y         [T,H] bf16 output, 16-byte aligned, 2H a multiple of 16.
- * workspace as produced by moe_layout.  When parts carry 128 KiB or more,
- *           all but each wavefront's first are handed out at run time from
- *           a counter in the workspace (separate from dispatch's): two
- *           combine calls that share a workspace must not run at the same
- *           time on different streams.
+ * workspace as produced by moe_layout.  Batches of more than 2^24 (token,
+ *           KiB of row) units take the plan's parts with tickets in the
+ *           workspace (separate from dispatch's): two such combine calls that
+ *           share a workspace must not run at the same time on different
+ *           streams.
  */
 int moe_combine(const uint64_t* expert_y, const float* topk_w, int64_t T, int H, int k,
                 int E, int R, const int32_t* topk_idx, const int32_t* pos,
@@ -346,9 +346,8 @@ int moe_combine(const uint64_t* expert_y, const float* topk_w, int64_t T, int H,
                 void* stream);
 
 /*
- * moe_combine_ex -- moe_combine with a work split (MOE_POLICY_BALANCED and
- * MOE_POLICY_STATIC: all parts assigned statically; MOE_POLICY_DYNAMIC as
- * for moe_dispatch_ex; others are MOE_EINVAL), the
+ * moe_combine_ex -- moe_combine with a work split (MOE_POLICY_BALANCED,
+ * MOE_POLICY_STATIC or MOE_POLICY_DYNAMIC; others are MOE_EINVAL), the
  * wavefront count and the optional per-wavefront trace of moe_dispatch_ex
  * (same rules, layout and clock).
  */

@@ -258,7 +258,7 @@ int combine_common(const uint64_t* expert_y, const float* topk_w, bool unit_weig
                    const int32_t* rank_offset, const int32_t* recv_cap, uint16_t* y,
                    const void* workspace, size_t workspace_bytes, size_t need_bytes,
                    size_t ticket_offset, uint32_t* status, int policy, int waves,
-                   uint64_t* trace, int trace_waves, int rows_hint, void* stream) {
+                   uint64_t* trace, int trace_waves, void* stream) {
   int rc = shape_ok(T, k, E, R);
   if (rc) return rc;
   if (H < 1 || !row_fits(2 * (int64_t)H)) return MOE_EINVAL;
@@ -290,7 +290,6 @@ int combine_common(const uint64_t* expert_y, const float* topk_w, bool unit_weig
   a.trace = trace;
   a.trace_waves = trace ? trace_waves : 0;
   a.launch_waves = waves;
-  a.rows_hint = rows_hint;
   a.tickets = reinterpret_cast<uint32_t*>(static_cast<char*>(const_cast<void*>(workspace)) +
                                           ticket_offset) + moe::kTicketGroupWords;
   return launched(moe::launch_combine(a, policy, as_stream(stream)));
@@ -310,7 +309,7 @@ int moe_combine_ex(const uint64_t* expert_y, const float* topk_w, int64_t T, int
   const moe::LayoutGeom g = moe::layout_geom(T, E);
   return combine_common(expert_y, topk_w, false, T, H, k, E, R, topk_idx, pos, rank_offset,
                         recv_cap, y, workspace, workspace_bytes, g.total, g.ticket_offset,
-                        status, policy, waves, trace, trace_waves, 0, stream);
+                        status, policy, waves, trace, trace_waves, stream);
 }
 
 int moe_combine(const uint64_t* expert_y, const float* topk_w, int64_t T, int H, int k, int E,
@@ -492,13 +491,9 @@ int moe_combine_dedup(const uint64_t* partial, int64_t T, int H, int k, int E, i
                       void* stream) {
   if (shape_ok(T, k, E, R)) return MOE_EINVAL;
   const moe::DedupGeom d = moe::dedup_geom(T, k, R);
-  // Sized and split as if every slot were a pair (its parts then count as
-  // large at prefill-sized batches and take the claimed split): on MI355X
-  // 6% faster at prefill and 11% at fp8 than sizing for half the slots,
-  // 2% slower at the large workload, the same at decode.
   return combine_common(partial, nullptr, true, T, H, k, E, R, topk_idx, tok_pos, tok_offset,
                         part_cap, y, workspace, workspace_bytes, d.total, d.g.ticket_offset,
-                        status, MOE_POLICY_BALANCED, 0, nullptr, 0, moe::slot_width(k), stream);
+                        status, MOE_POLICY_BALANCED, 0, nullptr, 0, stream);
 }
 
 }  // extern "C"

@@ -1,32 +1,25 @@
 // Combine: y[t] = bf16( sum_j w[t,j] * Y(row of slot j) ).
 //
-// Token-centric gather-reduce with the same byte-balanced partition as
-// dispatch (wavefront g of W takes parts g, g + W, ... of the plan; under the
-// default split every later part is handed out at run time instead when
-// parts are large, kClaimAllPartBytes).  Slot metadata for a batch
-// of 64/k tokens is resolved once, one slot per lane, and parked in LDS; for
-// each token the wavefront reads its k source rows and weights back at
-// uniform LDS addresses (waiting only on the LDS counter, never on pending
-// stores) and walks the output row in 1 KiB segments: every lane issues the
-// k independent 16-byte gathers of the next segment before it reduces the
-// current one and multiplies-adds in float32.  Output rows of 8-16 KiB are
-// kept in registers (8 bf16 values per lane and KiB) and stored as one burst
-// per token; other widths store each segment as it is reduced.  Each
-// output row has exactly one writer, so the reduction needs no atomics
-// (Section 6.1 accumulates on chip and writes back once).  Gathers and the
-// output stores are non-temporal: every byte is touched once, and on MI355X
-// keeping them out of the caches measured fastest for the whole
-// dispatch + combine step.
+// Default split (combine_unit_kernel): one wavefront per (token, 1 KiB slice
+// of its row) unit, launched in token order; the hardware hands units out as
+// wavefronts retire.  A wavefront resolves its token's k slots one per lane,
+// issues the k gathers of its slice together, multiplies and adds in float32
+// in slot order and stores the slice of y.  Each output byte has exactly one
+// writer, so the reduction needs no atomics (Section 6.1 accumulates on chip
+// and writes back once).  Gathers and stores are non-temporal: every byte is
+// touched once.
 //
-// Unused and capacity-dropped slots are redirected to a routed row of the
-// same token, their data is zeroed bitwise and their weight is 0 (a plain
-// multiply by 0 would turn an Inf in that row into NaN).  When the caller
-// expects many unused slots (the source-side sum of the per-peer path, where
-// a token's later slots on a peer carry no row), each slot is read through a
-// buffer resource instead: an unused slot's resource has an empty range, so
-// its loads return +0 without a memory access and need no mask.  That
-// measured 8% faster for that sum at Zipf-skewed prefill; with every slot
-// routed the redirect measured ~1% faster at decode and is kept there.
+// Explicit splits (combine_kernel; moe_combine_ex with a policy, a wavefront
+// count or a trace, and batches of more units than one grid holds):
+// persistent wavefronts over the byte-balanced plan (wavefront g of W takes
+// parts g, g + W, ... or claims them at run time).  Slot metadata for a batch
+// of 64/k tokens is resolved once, one slot per lane, and parked in LDS; for
+// each token the wavefront walks the output row in 1 KiB segments, the next
+// segment's gathers issued before the current one is reduced.  Output rows of
+// 8-16 KiB are kept in registers and stored as one burst per token.  Unused
+// and capacity-dropped slots are redirected to a routed row of the same
+// token, their data is zeroed bitwise and their weight is 0 (a plain multiply
+// by 0 would turn an Inf in that row into NaN).
 
 #include "moe_internal.h"
 
@@ -44,6 +37,15 @@ __device__ __forceinline__ void fma8(float (&acc)[8], const u32x4& v, float w) {
   acc[7] = __builtin_fmaf(w, bf16_hi(v.w), acc[7]);
 }
 
+__device__ __forceinline__ u32x4 pack8(const float (&acc)[8]) {
+  u32x4 o;
+  o.x = pack_bf16x2(acc[0], acc[1]);
+  o.y = pack_bf16x2(acc[2], acc[3]);
+  o.z = pack_bf16x2(acc[4], acc[5]);
+  o.w = pack_bf16x2(acc[6], acc[7]);
+  return o;
+}
+
 template <int KW>
 __device__ __forceinline__ void gather(u32x4 (&v)[KW], const uint8_t* const (&src)[KW],
                                        uint32_t off) {
@@ -53,13 +55,6 @@ __device__ __forceinline__ void gather(u32x4 (&v)[KW], const uint8_t* const (&sr
 
 // Buffer-resource loads (Rsrc) with cache policy 2, the non-temporal hint.
 constexpr int kLoadNonTemporal = 2;
-
-template <int KW>
-__device__ __forceinline__ void gather(u32x4 (&v)[KW], const Rsrc (&src)[KW], uint32_t off) {
-#pragma unroll
-  for (int j = 0; j < KW; ++j)
-    v[j] = __builtin_amdgcn_raw_buffer_load_b128(src[j], off, 0, kLoadNonTemporal);
-}
 
 // Weighted sum of one 1 KiB segment.  MASKED: unused slots read a routed
 // row of the same token; their data is zeroed (bitwise, so an Inf or NaN
@@ -79,20 +74,15 @@ __device__ __forceinline__ u32x4 reduce(const u32x4 (&v)[KW], const float (&wt)[
     }
     fma8(acc, x, wt[j]);
   }
-  u32x4 o;
-  o.x = pack_bf16x2(acc[0], acc[1]);
-  o.y = pack_bf16x2(acc[2], acc[3]);
-  o.z = pack_bf16x2(acc[4], acc[5]);
-  o.w = pack_bf16x2(acc[6], acc[7]);
-  return o;
+  return pack8(acc);
 }
 
 // One token's output row: full 1 KiB segments two at a time, then the
 // ragged tail.  The gathers of the next segment are issued before the
 // current one is reduced and stored, so waiting for them never waits for a
 // store (vector memory operations complete in issue order on this counter).
-template <int KW, bool MASKED, typename S>
-__device__ __forceinline__ void combine_row(uint8_t* dst, const S (&src)[KW],
+template <int KW, bool MASKED>
+__device__ __forceinline__ void combine_row(uint8_t* dst, const uint8_t* const (&src)[KW],
                                             const float (&wt)[KW],
                                             const uint32_t (&keep)[KW], uint32_t rb,
                                             uint32_t l16) {
@@ -132,11 +122,10 @@ __device__ __forceinline__ void store_row(uint8_t* dst, const u32x4 (&yr)[NSEG],
 // One token's output row of at most NSEG KiB, reduced into registers
 // (ceil(rb / 1 KiB) segments, the last one partial when rb is not a
 // multiple of 1 KiB) with the gathers two segments ahead as in combine_row,
-// then stored as one burst.  Masked whenever the slots are addressed by
-// pointer: the unrolled row is large, and the mask is four ANDs per slot and
-// segment (all ones for routed slots).
-template <int KW, int NSEG, bool MASKED, typename S>
-__device__ __forceinline__ void combine_row_burst(uint8_t* dst, const S (&src)[KW],
+// then stored as one burst.  Always masked: the unrolled row is large, and the
+// mask is four ANDs per slot and segment (all ones for routed slots).
+template <int KW, int NSEG>
+__device__ __forceinline__ void combine_row_burst(uint8_t* dst, const uint8_t* const (&src)[KW],
                                                   const float (&wt)[KW],
                                                   const uint32_t (&keep)[KW], uint32_t rb,
                                                   uint32_t l16) {
@@ -148,16 +137,15 @@ __device__ __forceinline__ void combine_row_burst(uint8_t* dst, const S (&src)[K
     if ((uint32_t)s < ns) {
       const uint32_t on = l16 + (uint32_t)(s + 1) * kWaveBytes;
       if (on < rb) gather<KW>(v[(s + 1) & 1], src, on);
-      yr[s] = reduce<KW, MASKED>(v[s & 1], wt, keep);
+      yr[s] = reduce<KW, true>(v[s & 1], wt, keep);
     }
   }
   store_row<NSEG>(dst, yr, rb, l16);
 }
 
 // KW: slots resolved per token (>= k).  NSEG > 0: rows of at most NSEG KiB,
-// each held in registers and stored as one burst (combine_row_burst).  BUF:
-// slots read through buffer resources, unused ones with an empty range.
-template <int KW, bool DYN, int NSEG, bool BUF>
+// each held in registers and stored as one burst (combine_row_burst).
+template <int KW, bool DYN, int NSEG>
 __global__ __launch_bounds__(kBlock) void combine_kernel(CombineArgs a) {
   // Per-slot source row and weight of the current batch, one entry per lane
   // of each wavefront (0 = slot not combined), padded with zeros so a token
@@ -261,19 +249,8 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(CombineArgs a) {
         for (int j = 0; j < KW; ++j)
           if (!keep[j]) src[j] = reinterpret_cast<const uint8_t*>(first);
       }
-      if constexpr (BUF) {
-        Rsrc rs[KW];
-#pragma unroll
-        for (int j = 0; j < KW; ++j)
-          rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(src[j]), (short)0,
-                                                    keep[j] ? (int)rb : 0, kRsrcWord3);
-        if constexpr (NSEG > 0) {
-          combine_row_burst<KW, NSEG, false>(dst, rs, wt, keep, rb, l16);
-        } else {
-          combine_row<KW, false>(dst, rs, wt, keep, rb, l16);
-        }
-      } else if constexpr (NSEG > 0) {
-        combine_row_burst<KW, NSEG, true>(dst, src, wt, keep, rb, l16);
+      if constexpr (NSEG > 0) {
+        combine_row_burst<KW, NSEG>(dst, src, wt, keep, rb, l16);
       } else if (all) {
         combine_row<KW, false>(dst, src, wt, keep, rb, l16);
       } else {
@@ -288,16 +265,14 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(CombineArgs a) {
   trace_wave(a.trace, a.trace_waves, g, t_start, lane);
 }
 
-template <int KW, bool DYN, int NSEG, bool BUF>
+template <int KW, bool DYN, int NSEG>
 hipError_t launch_kw(CombineArgs a, int64_t in_flight, hipStream_t stream) {
-  const void* fn = reinterpret_cast<const void*>(&combine_kernel<KW, DYN, NSEG, BUF>);
-  // KW gathers of 1 KiB for each of the two segments in flight (of which
-  // rows_hint read routed rows when the caller expects masked slots)
-  const int64_t rows = a.rows_hint > 0 ? a.rows_hint : KW;
+  const void* fn = reinterpret_cast<const void*>(&combine_kernel<KW, DYN, NSEG>);
+  // KW gathers of 1 KiB for each of the two segments in flight
   const int waves = a.launch_waves > 0
                         ? a.launch_waves
-                        : copy_waves(fn, 2 * rows * kWaveBytes, in_flight, 512);
-  hipLaunchKernelGGL((combine_kernel<KW, DYN, NSEG, BUF>), dim3(waves / kWavesPerBlock),
+                        : copy_waves(fn, 2ll * KW * kWaveBytes, in_flight, 512);
+  hipLaunchKernelGGL((combine_kernel<KW, DYN, NSEG>), dim3(waves / kWavesPerBlock),
                      dim3(kBlock), 0, stream, a);
   return hipGetLastError();
 }
@@ -309,22 +284,12 @@ hipError_t launch_kw(CombineArgs a, int64_t in_flight, hipStream_t stream) {
 // registers) store each segment as it is reduced.
 constexpr int kBurstSegs = 16;
 
-// Buffer-resource slots (BUF) when the caller expects unused slots
-// (rows_hint > 0) and the KW resources fit the scalar registers (KW <= 8).
-template <int KW, bool DYN, bool BUF>
-hipError_t launch_burst(const CombineArgs& a, int64_t in_flight, hipStream_t stream) {
-  if (KW <= 8 && a.row_bytes >= 8ll * kWaveBytes &&
-      a.row_bytes <= (int64_t)kBurstSegs * kWaveBytes)
-    return launch_kw<KW, DYN, (KW <= 8 ? kBurstSegs : 0), BUF>(a, in_flight, stream);
-  return launch_kw<KW, DYN, 0, BUF>(a, in_flight, stream);
-}
-
 template <int KW, bool DYN>
 hipError_t launch_rows(const CombineArgs& a, int64_t in_flight, hipStream_t stream) {
-  if constexpr (KW <= 8) {
-    if (a.rows_hint > 0) return launch_burst<KW, DYN, true>(a, in_flight, stream);
-  }
-  return launch_burst<KW, DYN, false>(a, in_flight, stream);
+  if (KW <= 8 && a.row_bytes >= 8ll * kWaveBytes &&
+      a.row_bytes <= (int64_t)kBurstSegs * kWaveBytes)
+    return launch_kw<KW, DYN, (KW <= 8 ? kBurstSegs : 0)>(a, in_flight, stream);
+  return launch_kw<KW, DYN, 0>(a, in_flight, stream);
 }
 
 template <bool DYN>
@@ -338,11 +303,152 @@ hipError_t launch_dyn(const CombineArgs& a, int64_t in_flight, hipStream_t strea
   }
 }
 
+// One wavefront per (token, slice of S KiB of its row); KB: slots gathered
+// together (k when k <= 8, else 8 at a time).
+//
+// Bound by HBM reads (k gathers per store).  As in dispatch the number of
+// bytes in flight over the chip sets the rate, from both sides, so the launch
+// limits the resident wavefronts (combine_unit_waves) and a slice is as
+// narrow as keeps a few gathers in flight per wavefront: S = 1 from k = 3,
+// at most 2 for k = 2 and 4 for k = 1 (16384 x 14 KiB on MI355X, us at S = 1 / 2 / 4:
+// k = 1 120 87 84, k = 2 133 118 119, k = 4 192 196 201, k = 8 340 360 360).
+// Slots are read through buffer resources: an unused or capacity-dropped
+// slot's resource has an empty range, so its load returns +0 without touching
+// memory, and so does the part of a slice past the row's end.  Measured on
+// MI355X against the persistent split below (us before -> after, GB/s of
+// algorithmic bytes after):
+//   16384 x 14 KiB, k = 8, Zipf 1.2 routing   366 -> 340  (6220)
+//   32768 x 8 KiB, k = 8, Zipf 1.5            431 -> 391  (6180)
+//   8192 x 14 KiB, k = 16, uniform            444 -> 338  (5900)
+//   16384 x 10 KiB, k = 6, uniform            221 -> 196  (5990)
+//   4096 x 14 KiB, k = 8, uniform             90.3 -> 88.0 (6010)
+//   32768 x 512 B, k = 8                      44.4 -> 28.3 (5340)
+//   16384 x 14 KiB, k = 1, uniform            104 -> 80  (5850)
+//   512 x 14 KiB, k = 8                       25.7 -> 13.0
+template <int KB, int S>
+__global__ __launch_bounds__(kBlock) void combine_unit_kernel(CombineArgs a, int slices,
+                                                              int units) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int u = uniform(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave);
+  if (u >= units) return;
+  const int t = u / slices, q = u - t * slices;
+  const uint32_t rb = (uint32_t)a.row_bytes;
+  const int k = a.k;
+  const uint32_t o0 = (uint32_t)q * (S * kWaveBytes) + lane * kVecBytes;
+  int p = -1, e = 0;
+  float w = 1.0f;   // null weights: unit weights
+  if (lane < k) {
+    const int64_t s = (int64_t)t * k + lane;
+    p = a.pos[s];
+    e = a.topk_idx[s];
+    if (a.topk_w) w = a.topk_w[s];
+  }
+  uint64_t srow = 0;
+  float wl = 0.0f;
+  uint32_t st = 0;
+  if (p >= 0) {
+    const int r = e / a.L;
+    if ((unsigned)r >= (unsigned)a.R) {
+      st |= MOE_STATUS_BAD_INDEX;   // pos and topk_idx disagree: weight 0
+    } else {
+      const int local = p - a.rank_offset[r];
+      const int cap = a.recv_cap[r];
+      const uint64_t ry = a.expert_y[r];
+      if (local >= 0 && local < cap) {
+        srow = ry + (uint64_t)local * (uint64_t)rb;
+        wl = w;
+      } else {
+        st |= MOE_STATUS_CAPACITY;
+      }
+    }
+  }
+  float acc[S][8];
+#pragma unroll
+  for (int c = 0; c < S; ++c)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[c][i] = 0.0f;
+  // lanes past k hold no slot, so the last group of 8 may be partly empty
+  for (int j0 = 0; j0 < k; j0 += KB) {
+    u32x4 v[KB][S];
+#pragma unroll
+    for (int j = 0; j < KB; ++j) {
+      const uint64_t base = readlane64(srow, j0 + j);
+      const Rsrc rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<uint8_t*>(base),
+                                                        (short)0, base ? (int)rb : 0, kRsrcWord3);
+#pragma unroll
+      for (int c = 0; c < S; ++c)
+        v[j][c] = __builtin_amdgcn_raw_buffer_load_b128(rs, o0 + c * kWaveBytes, 0,
+                                                        kLoadNonTemporal);
+    }
+#pragma unroll
+    for (int j = 0; j < KB; ++j) {
+      const float wj = readlane_f32(wl, j0 + j);
+#pragma unroll
+      for (int c = 0; c < S; ++c) fma8(acc[c], v[j][c], wj);
+    }
+  }
+  uint8_t* dst = reinterpret_cast<uint8_t*>(a.y) + (int64_t)t * rb;
+#pragma unroll
+  for (int c = 0; c < S; ++c) {
+    const uint32_t off = o0 + c * kWaveBytes;
+    if (off < rb) st16_stream(dst + off, pack8(acc[c]));
+  }
+  if (q == 0) {   // one wavefront reports a token
+    st = wave_or(st);
+    if (st && lane == 0) atomicOr(a.status, st);
+  }
+}
+
+// Resident wavefronts per compute unit: about 160 KiB of gathers in flight,
+// at least 16 wavefronts.  Measured on MI355X (us at 32 / 28 / 24 / 20 / 16 /
+// 12 wavefronts): k = 8 Zipf, 14 KiB rows 369 - 354 340 337 342; k = 8 Zipf,
+// 8 KiB rows 422 - 409 391 391 414; k = 6 198 196 197 201 207 -; k = 4 192 194
+// 199 208 221 -; k = 16 342 342 343 342 338 355; k = 8, 512 B rows 28.3 29.2
+// 30.4 32.3 34.9 46.
+int combine_unit_waves(int64_t wave_bytes) {
+  const int64_t w = ((160ll << 10) / wave_bytes + 3) / 4 * 4;
+  return w < 16 ? 16 : w > 32 ? 32 : (int)w;
+}
+
+template <int KB, int S>
+hipError_t launch_unit_as(const CombineArgs& a, hipStream_t stream) {
+  const int slices = (int)((row_slices(a.row_bytes) + S - 1) / S);
+  const int units = (int)a.tokens * slices;
+  const int64_t width = a.row_bytes < S * kWaveBytes ? a.row_bytes : S * kWaveBytes;
+  hipLaunchKernelGGL((combine_unit_kernel<KB, S>),
+                     dim3((units + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock),
+                     wave_limit_lds(combine_unit_waves(a.k * width), kWavesPerBlock), stream, a,
+                     slices, units);
+  return hipGetLastError();
+}
+
+template <int KB>
+hipError_t launch_unit(const CombineArgs& a, hipStream_t stream) {
+  if (KB == 1 && a.row_bytes > 2 * kWaveBytes) return launch_unit_as<KB, KB == 1 ? 4 : 1>(a, stream);
+  if (KB <= 2 && a.row_bytes > kWaveBytes) return launch_unit_as<KB, KB <= 2 ? 2 : 1>(a, stream);
+  return launch_unit_as<KB, 1>(a, stream);
+}
+
+hipError_t launch_units(const CombineArgs& a, hipStream_t stream) {
+  switch (a.k) {
+    case 1: return launch_unit<1>(a, stream);
+    case 2: return launch_unit<2>(a, stream);
+    case 3: return launch_unit<3>(a, stream);
+    case 4: return launch_unit<4>(a, stream);
+    case 5: return launch_unit<5>(a, stream);
+    case 6: return launch_unit<6>(a, stream);
+    case 7: return launch_unit<7>(a, stream);
+    default: return launch_unit<8>(a, stream);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_combine(const CombineArgs& a, int policy, hipStream_t stream) {
-  const int64_t rows = a.rows_hint > 0 ? a.rows_hint : a.k;
-  const bool large = claim_all_parts(a.tokens, a.row_bytes, rows);
+  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace &&
+      a.tokens * row_slices(a.row_bytes) <= kMaxUnits)
+    return launch_units(a, stream);
+  const bool large = claim_all_parts(a.tokens, a.row_bytes, a.k);
   const bool claim = policy == MOE_POLICY_DYNAMIC || (policy == MOE_POLICY_BALANCED && large);
   // Small parts (decode-sized batches) measured 2% faster for combine, and
   // the dispatch after it too, with twice the gathers in flight; large

@@ -89,6 +89,23 @@ __host__ __forceinline__ bool claim_all_parts(int64_t tokens, int64_t row_bytes,
   return tokens * row_bytes * (1 + rows) / MOE_PLAN_PARTS >= min_part_bytes;
 }
 
+// Unit kernels (the default split of the copy kernels): one wavefront per
+// (token, 1 KiB slice or slices of its row), launched in token order.
+__host__ __forceinline__ int64_t row_slices(int64_t row_bytes) {
+  return (row_bytes + kWaveBytes - 1) / kWaveBytes;
+}
+// Units one launch takes: a grid holds fewer than 2^32 work items in x.
+constexpr int64_t kMaxUnits = 1 << 24;
+
+// Dynamic LDS that keeps at most `waves` wavefronts of a kernel with
+// wpb-wavefront workgroups (and no LDS of its own) resident on a compute
+// unit, 0 for no limit.  A compute unit has 160 KiB, allocated in granules of
+// 1280 bytes (128 of them).
+__host__ __forceinline__ unsigned wave_limit_lds(int waves, int wpb) {
+  const int blocks = waves / wpb > 0 ? waves / wpb : 1;
+  return blocks * wpb >= 32 ? 0u : (unsigned)(128 / blocks * 1280);
+}
+
 // fixed_cap < 0: packed layout; >= 0: fixed windows of fixed_cap rows.
 // peer_L > 0: topk_idx holds experts in [0, E * peer_L) and the layout is
 // over the E peers, one row per (token, peer) pair (first slot of the pair).
@@ -140,7 +157,6 @@ struct CombineArgs {
   uint16_t* y;
   const int32_t* bound;
   int32_t launch_waves;
-  int32_t rows_hint;           // rows gathered per token, for copy_waves (0: all KW)
   uint32_t* status;
   uint64_t* trace;
   int32_t trace_waves;
@@ -148,6 +164,8 @@ struct CombineArgs {
   int32_t R;                   // ranks (entries of expert_y, rank_offset, recv_cap)
 };
 
+// MOE_POLICY_BALANCED without a wavefront count or a trace takes the unit
+// kernel, everything else the persistent split.
 hipError_t launch_combine(const CombineArgs& a, int policy, hipStream_t stream);
 
 struct ExpertArgs {

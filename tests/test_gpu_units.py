@@ -1,0 +1,68 @@
+"""The (token, slice) unit kernels of the default split: edges of slices and
+slot groups, against the oracle and, bit for bit, against the persistent
+split of the same library (MOE_POLICY_STATIC)."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2607_26444_amd import moe
+    moe.lib()
+
+
+# T, H, E, R, k, payload, mask, short: row widths one 16-byte piece around
+# 1, 2 and 4 KiB (a slice, and the widths from which k = 2 and k = 1 take two
+# and four slices per wavefront); k around the groups of 8 gathers; one token.
+CASES = [
+    (1, 7168, 256, 64, 8, wl.BF16, 0.0, False),
+    (3, 8, 4, 2, 1, wl.BF16, 0.0, False),
+    (65, 504, 16, 4, 1, wl.BF16, 0.1, True),
+    (65, 512, 16, 4, 2, wl.BF16, 0.1, False),
+    (65, 520, 16, 4, 2, wl.BF16, 0.0, True),
+    (63, 1016, 16, 8, 1, wl.BF16, 0.2, False),
+    (63, 1032, 16, 8, 1, wl.BF16, 0.0, True),
+    (63, 2056, 16, 8, 1, wl.BF16, 0.2, False),
+    (130, 3080, 32, 8, 3, wl.BF16, 0.1, True),
+    (130, 1544, 32, 32, 5, wl.BF16, 0.3, False),
+    (130, 1032, 64, 16, 7, wl.BF16, 0.3, True),
+    (130, 1032, 64, 16, 9, wl.BF16, 0.3, True),
+    (70, 520, 64, 16, 16, wl.BF16, 0.5, False),
+    (70, 520, 64, 16, 17, wl.BF16, 0.5, True),
+    (70, 520, 1024, 1024, 32, wl.BF16, 0.5, True),
+    (1, 128, 8, 2, 8, wl.FP8_E4M3, 0.0, False),
+    (130, 1152, 32, 8, 3, wl.FP8_E4M3, 0.2, True),      # 36-byte scale rows, pitch 128
+    (130, 7168, 64, 16, 8, wl.FP8_E4M3, 0.1, True),     # 224-byte scale rows, pitch 256
+    (40, 33280, 16, 4, 4, wl.FP8_E4M3, 0.1, False),     # scale rows of more than 1 KiB
+]
+
+
+# fp8 scale rows at the harness's pitch (whole 128-byte lines) and packed
+PACKED = [c + (p,) for p in (False, True) for c in CASES if not p or c[5] == wl.FP8_E4M3]
+
+
+@pytest.mark.parametrize("T,H,E,R,k,payload,mask,short,packed", PACKED)
+def test_units_match_oracle_and_persistent_split(T, H, E, R, k, payload, mask, short, packed):
+    import gpu_harness as h
+    from paper_2607_26444_amd import moe
+    from test_gpu_parity import _full_parity
+    cfg = wl.custom(T, H, E, R, k, payload=payload, zipf_s=1.2, seed=T + H + k)
+    inp = wl.make_inputs(cfg)
+    idx = wl.mask_slots(inp["topk_idx"], mask, seed=k) if mask else None
+    delta = [-(r % 2) for r in range(R)] if short else None
+    pitch = 0 if packed else None
+    kw = dict(idx=idx, spare_rows=0 if short else 1, cap_delta=delta, scale_pitch=pitch)
+    run, _ = _full_parity(cfg, inp, **kw)
+    again = h.GpuRun(cfg, inp, topk_idx=idx, spare_rows=kw["spare_rows"], cap_delta=delta,
+                     scale_pitch=pitch, policy=moe.MOE_POLICY_STATIC,
+                     combine_policy=moe.MOE_POLICY_STATIC)
+    assert np.array_equal(run.y, again.y)
+    assert run.layout["status"] == again.layout["status"]
