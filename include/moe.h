@@ -96,11 +96,12 @@ extern "C" {
 #define MOE_FP8_BLOCK 128
 
 /* Number of parts P of the byte-balanced partition plan (parts of equal byte
- * cost).  moe_dispatch and moe_combine launch W wavefronts, W a power of
- * two that divides P (dispatch 256 to 4096, combine 512 to 4096, sized from
- * the bytes each wavefront keeps in flight).  Wavefront g starts at part g;
- * later parts are either strided statically (g+W, g+2W, ...) or handed out
- * at run time in plan order, as MOE_POLICY_BALANCED describes.
+ * cost), for the explicit splits of moe_dispatch_ex / moe_combine_ex, the
+ * expansion and the partial combine of the per-peer path.  They launch W
+ * wavefronts, W a power of two that divides P, sized from the bytes each
+ * wavefront keeps in flight.  Wavefront g starts at part g; later parts are
+ * either strided statically (g+W, g+2W, ...) or handed out at run time in
+ * plan order.
  * 12288 = 3 * 2^12 also divides evenly over 256 compute units at 4, 8, 12,
  * 16, 24 or 48 wavefronts each. */
 #define MOE_PLAN_PARTS 12288
@@ -247,12 +248,10 @@ int moe_layout_fixed(const int32_t* topk_idx, int64_t T, int k, int E, int R, in
  *           wavefronts write partially; packed 224-byte rows cost ~30 us more
  *           per 131k rows on MI355X.
  * recv_cap  [R] int32 capacity of each region in rows.
- * topk_idx, pos, rank_offset, workspace: as produced by moe_layout.  Parts
- *           of the plan are handed out at run time from a counter in the
- *           workspace (all but each wavefront's first when parts carry 64
- *           KiB or more, else the second half; MOE_POLICY_BALANCED of
- *           moe_dispatch_ex): two dispatch calls that share a workspace must
- *           not run at the same time on different streams.
+ * topk_idx, pos, rank_offset, workspace: as produced by moe_layout.  Batches
+ *           of more than 2^24 (token, KiB of row) units take the plan's parts
+ *           with tickets in the workspace: two such dispatch calls that share
+ *           a workspace must not run at the same time on different streams.
  * Bytes of a region beyond the rows dispatch writes are left untouched.
  */
 int moe_dispatch(const void* x, const float* x_scales, int dtype, int64_t T, int H,
@@ -264,15 +263,17 @@ int moe_dispatch(const void* x, const float* x_scales, int dtype, int64_t T, int
 
 /* Work-split policies of moe_dispatch_ex / moe_combine_ex (all give
  * bit-identical regions and identical y). */
-#define MOE_POLICY_BALANCED 0 /* byte-balanced parts, the library's choice: when a
+#define MOE_POLICY_BALANCED 0 /* the library's choice (moe_dispatch, moe_combine): one
+                               * wavefront per token and KiB of row.  With a
+                               * wavefront count or a trace, and for more than 2^24
+                               * such units, byte-balanced parts of the plan: when a
                                * part carries 64 KiB (dispatch) or 128 KiB (combine)
                                * or more on average, every part after each
                                * wavefront's first is handed out at run time;
                                * smaller parts: dispatch assigns the first half
                                * statically and hands the rest out at run time (all
                                * statically when a wavefront would own fewer than 8
-                               * parts), combine assigns all statically
-                               * (moe_dispatch, moe_combine) */
+                               * parts), combine assigns all statically */
 #define MOE_POLICY_ROWS 1     /* pull: the N routed rows split evenly over wavefronts */
 #define MOE_POLICY_BY_RANK 2  /* pull: a fixed group of W/R wavefronts per rank */
 #define MOE_POLICY_DYNAMIC 3  /* push; every part after the first handed out at run time */

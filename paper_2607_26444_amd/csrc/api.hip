@@ -198,6 +198,8 @@ int dispatch_common(const void* x, const float* x_scales, int dtype, int64_t T, 
   a.row_bytes = row_bytes;
   a.scale_row_bytes = scale_row;
   a.scale_pitch = fp8 ? pitch : 0;
+  a.scales16 = fp8 && scale_row % 16 == 0 && pitch % 16 == 0 && pitch <= moe::kWaveBytes &&
+               aligned(x_scales, 16);
   a.k = k;
   a.L = E / R;
   a.topk_idx = topk_idx;

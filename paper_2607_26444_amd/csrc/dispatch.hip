@@ -1,34 +1,25 @@
 // Dispatch: copy each routed token row into its rank's receive region.
 //
-// Work split (Section 6.2 with one memory tier, Appendix D third level):
-// moe_layout leaves MOE_PLAN_PARTS contiguous token ranges of equal byte
-// cost (a token costs one row read plus one row write per routed slot).  The
-// kernel launches W wavefronts (a power of two chosen by copy_waves) and
-// wavefront g takes parts g, g + W, g + 2W, ...: every wavefront moves the
-// same number of bytes no matter how skewed the routing is (a hot expert only
-// changes where rows land, not who copies them), and at any moment the W
-// wavefronts work on neighbouring parts, so x is read and each expert window
-// is written as one advancing front instead of W scattered streams (on
-// MI355X that measured ~5% faster for dispatch and ~7% for combine than
-// giving each wavefront one contiguous run of parts).  Equal bytes are not
-// equal time on a shared memory system, so under the default split parts
-// are also handed out at run time from a workspace counter, in plan order
-// (the front is kept): every part after each wavefront's first when parts
-// are large (kClaimAllPartBytes), the second half of the parts otherwise.
+// Default split (dispatch_unit_kernel): the batch is cut into (token, 1 KiB
+// slice of its row) units, one wavefront each, launched in token order.  A
+// wavefront loads its slice once and stores it to the token's k destination
+// rows, so x is read exactly once, and the hardware hands units out as
+// wavefronts retire: every compute unit takes the next work when it is free,
+// whatever the routing (a hot expert only changes where rows land), with no
+// plan, no tickets and no metadata beyond the token's own k slots.  The
+// fourteen slices of a 14 KiB row start together, so each destination row
+// still reaches memory as one run, and a batch of a few tokens spreads over
+// the chip by its slices.
 //
-// Push direction: a wavefront reads its token's row from x once into
-// registers (16 bytes per lane per 1 KiB segment, so a 14 KiB row is 14
-// dwordx4 loads in flight per lane) and stores it to each of the token's k
-// destinations.  x is read exactly once; every destination row is written
-// by exactly one wavefront with full 1 KiB coalesced stores, non-temporal for
-// rows wider than 8 KiB (written once, not read again here; with the
-// advancing front this measured 8-12% faster than ordinary stores on
-// MI355X) and ordinary for narrower rows (store_row16).  Slot metadata
-// (pos, expert, region base, capacity) for a batch of 64/k tokens is loaded
-// once, one slot per lane, and parked in LDS; the copy loop reads each
-// destination back at a uniform LDS address, so no global load of metadata
-// (whose wait would also wait for every pending row store) sits between
-// row stores.
+// Explicit splits (dispatch_kernel; moe_dispatch_ex with a policy, a
+// wavefront count or a trace, and batches of more units than one grid holds):
+// persistent wavefronts over the byte-balanced plan (Section 6.2 with one
+// memory tier, Appendix D third level).  moe_layout leaves MOE_PLAN_PARTS
+// contiguous token ranges of equal byte cost; wavefront g of W takes parts g,
+// g + W, g + 2W, ... or claims parts in plan order at run time.  A wavefront
+// reads its token's whole row into registers and stores it to each of the k
+// destinations; slot metadata for a batch of 64/k tokens is loaded once, one
+// slot per lane, and parked in LDS.
 
 #include "moe_internal.h"
 
@@ -207,6 +198,173 @@ __global__ __launch_bounds__(kBlock) void dispatch_kernel(DispatchArgs a) {
   st = wave_or(st);
   if (st && lane == 0) atomicOr(a.status, st);
   trace_wave(a.trace, a.trace_waves, g, t_start, lane);
+}
+
+template <bool NT>
+__device__ __forceinline__ void store16(void* p, u32x4 v) {
+  if constexpr (NT)
+    st16_stream(p, v);
+  else
+    st16(p, v);
+}
+
+// One wavefront per (token, 1 KiB slice of its row).
+//
+// Bound by HBM writes (one read per k writes).  What sets the rate is how
+// many row stores are in flight over the chip: too few leave HBM idle, too
+// many open more destination rows than its pages serve well, so the launch
+// limits the resident wavefronts (dispatch_unit_waves).  A slice of 1 KiB
+// (one 16-byte store per lane and destination) holds the fewest bytes per
+// wavefront; 2 and 4 KiB slices measured 0-3% slower at their best limit.
+// Metadata is the token's k slots, one lane each, read by every slice (one
+// line, from the caches); the destinations are read back by lane, so neither
+// LDS nor a barrier is needed.  Measured on MI355X against the persistent
+// split below (us before -> after, GB/s of algorithmic bytes after):
+//   16384 x 14 KiB, k = 8, Zipf 1.2 routing   384 -> 358  (5900)
+//   32768 x 8 KiB, k = 8, Zipf 1.5            444 -> 410  (5890)
+//   8192 x 14 KiB, k = 16, uniform            524 -> 400  (5000)
+//   32768 x 512 B, k = 8                      41.3 -> 26  (5800)
+//   512 x 14 KiB, k = 8                       22.6 -> 12.4
+//   4096 x 14 KiB, k = 8, uniform, x cached   91.5 -> 92   (5750)
+//   8192 x 7 KiB fp8, k = 8, uniform / Zipf   109 / 104 -> 100 / 89
+//   16384 x 8 KiB, k = 8, uniform             221 -> 229  (5270): 256 windows
+//   of wide rows written at once are the one range where it is slower
+// NT: non-temporal stores; ordinary ones were 0-30% slower (8 KiB rows Zipf
+// 413 -> 434, 2 KiB rows 53 -> 67, 14 KiB rows at 4096 tokens 94 -> 102)
+// except for very large fp8 batches (kScaledStreamBytes).
+//
+// SCALES: the wavefront of slice 0 also carries the token's scale row: sized
+// in 16-byte multiples and at most 1 KiB, its pitched bytes are spread over
+// groups of `pieces` lanes, one group per destination, so one store
+// instruction writes 64 / pieces scale rows whole.
+template <bool SCALES, bool NT>
+__global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, int slices,
+                                                               int units) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int u = uniform(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
+  if (u >= units) return;
+  const int t = u / slices, q = u - t * slices;
+  const uint32_t rb = (uint32_t)a.row_bytes;
+  const uint32_t sb = (uint32_t)a.scale_row_bytes;
+  const uint32_t sp = (uint32_t)a.scale_pitch;
+  const int k = a.k;
+  const uint32_t off = (uint32_t)q * kWaveBytes + lane * kVecBytes;
+  int p = -1, e = 0;
+  if (lane < k) {
+    p = a.pos[(int64_t)t * k + lane];
+    e = a.topk_idx[(int64_t)t * k + lane];
+  }
+  u32x4 v = {0u, 0u, 0u, 0u}, sv = {0u, 0u, 0u, 0u};
+  if (off < rb) v = ld16(a.x + (int64_t)t * rb + off);
+  const uint8_t* ssrc = SCALES ? a.x_scales + (int64_t)t * sb : nullptr;
+  const bool scales_here = SCALES && q == 0;
+  const int pieces = (int)sp / kVecBytes;
+  const bool s16 = a.scales16;
+  int sj = 0;           // this lane's destination within a group store
+  uint32_t soff = 0;    // ... and its bytes of the scale row
+  if (scales_here && s16) {
+    sj = lane / pieces;
+    soff = (uint32_t)(lane - sj * pieces) * kVecBytes;
+    if (soff < sb) sv = ld16(ssrc + soff);
+  }
+  uint64_t dst = 0, sdst = 0;
+  uint32_t st = 0;
+  if (p >= 0) {
+    const int r = e / a.L;
+    if ((unsigned)r >= (unsigned)a.R) {
+      st |= MOE_STATUS_BAD_INDEX;   // pos and topk_idx disagree: not copied
+    } else {
+      const int local = p - a.rank_offset[r];
+      const int cap = a.recv_cap[r];
+      const uint64_t rx = a.recv_x[r];
+      uint64_t rs = 0;
+      if (scales_here) rs = a.recv_scales[r];
+      if (local >= 0 && local < cap) {
+        dst = rx + (uint64_t)local * rb;
+        sdst = rs + (uint64_t)local * sp;
+      } else {
+        st |= MOE_STATUS_CAPACITY;
+      }
+    }
+  }
+  for (int j = 0; j < k; ++j) {
+    uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j));
+    if (d && off < rb) store16<NT>(d + off, v);
+  }
+  if (scales_here) {
+    if (s16) {
+      const int per = kWave / pieces;
+      for (int j0 = 0; j0 < k; j0 += per) {
+        const int j = j0 + sj;
+        uint8_t* d = reinterpret_cast<uint8_t*>(
+            __shfl((unsigned long long)sdst, j & (kWave - 1), kWave));
+        if (sj < per && j < k && d) store16<NT>(d + soff, sv);
+      }
+    } else {
+      // other scale-row sizes: one float32 per lane per pass
+      for (uint32_t o = 0; o < sp; o += kWave * 4) {
+        const uint32_t so = o + lane * 4;
+        uint32_t s4 = 0;
+        if (so < sb) s4 = ld4(ssrc + so);
+        for (int j = 0; j < k; ++j) {
+          uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(sdst, j));
+          if (d && so < sp) st4(d + so, s4);
+        }
+      }
+    }
+  }
+  if (q == 0) {   // one wavefront reports a token
+    st = wave_or(st);
+    if (st && lane == 0) atomicOr(a.status, st);
+  }
+}
+
+// Resident wavefronts per compute unit for `rows` stores of 1 KiB per
+// wavefront: about 96 KiB of stores in flight for 8 (12 wavefronts), more
+// wavefronts for fewer, whose lives are mostly load latency.  Pair rows are
+// sized for about half the slots: under Zipf routing 12 wavefronts made the
+// per-peer chain 3% slower than 18 (1594 -> 1545 us at 16384 x 14 KiB), under
+// uniform routing 0.7% faster (593 -> 597 at 4096 tokens).  Measured
+// on MI355X (16384 x 14 KiB; us at 32 / 18 / 14 / 12 / 9 wavefronts):
+//   k = 8, Zipf  388 377 360 358 392     k = 8, uniform  421 413 408 397 -
+//   k = 6 (10 KiB rows)  229 219 215 224 -      k = 4  228 216 230 247 -
+//   k = 2  134 145 167 183 -     k = 16 (8192 tokens)  404 385 399 400 400
+// bf16 batches of at most 96 MiB of x, whose loads the Infinity Cache mostly
+// serves and whose lives are shorter, take two fewer from 8 rows on (whole
+// steps of 4096 x 14 KiB, k = 8, us at 12 / 10 / 8 wavefronts: 192.1 191.2
+// 191.4 with x cached, 203.2 201.7 209.4 with x in HBM).
+int dispatch_unit_waves(int64_t rows, bool small_x) {
+  if (rows < 8) return (int)(48 / rows) + 6;
+  return small_x ? 10 : 12;
+}
+
+// Rows with scale rows are stored non-temporally up to this many row bytes in
+// all and with ordinary stores beyond (fp8 7 KiB rows, k = 8, us
+// non-temporal / ordinary: 4096 tokens 49 / 54, 8192 100 / 107, 12288 148 /
+// 152; at 16384, 896 MiB, uniform routing 211 / 205 and Zipf 187 / 194, where
+// the persistent split took 210 and 199).
+constexpr int64_t kScaledStreamBytes = 768ll << 20;
+
+template <bool SCALES>
+hipError_t launch_unit(const DispatchArgs& a, hipStream_t stream) {
+  const int slices = (int)row_slices(a.row_bytes);
+  const int units = (int)a.tokens * slices;
+  // One wavefront per workgroup frees its slot as soon as it is done.  With
+  // scale rows the slice-0 wavefront lives longer, and workgroups of four
+  // measured better at the same limit (fp8, 16384 x 7 KiB: uniform 219 -> 208
+  // us, Zipf 202 -> 186).
+  const int wpb = SCALES ? kWavesPerBlock : 1;
+  const int64_t rows = a.rows_hint > 0 ? a.rows_hint : a.k;
+  const dim3 grid((units + wpb - 1) / wpb), block(wpb * kWave);
+  const bool small_x = !SCALES && a.tokens * a.row_bytes <= (96ll << 20);
+  const unsigned lds = wave_limit_lds(dispatch_unit_waves(rows, small_x), wpb);
+  if (SCALES && a.tokens * rows * a.row_bytes > kScaledStreamBytes)
+    hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, !SCALES>), grid, block, lds, stream, a,
+                       slices, units);
+  else
+    hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true>), grid, block, lds, stream, a, slices,
+                       units);
+  return hipGetLastError();
 }
 
 // Pull dispatch for the partitioning study: a wavefront walks a range of
@@ -404,6 +562,9 @@ hipError_t launch_scales(const DispatchArgs& a, int policy, hipStream_t stream) 
 }  // namespace
 
 hipError_t launch_dispatch(const DispatchArgs& a, int policy, hipStream_t stream) {
+  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace &&
+      a.tokens * row_slices(a.row_bytes) <= kMaxUnits)
+    return a.x_scales ? launch_unit<true>(a, stream) : launch_unit<false>(a, stream);
   return a.x_scales ? launch_scales<true>(a, policy, stream)
                     : launch_scales<false>(a, policy, stream);
 }

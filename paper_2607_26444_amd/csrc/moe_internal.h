@@ -122,6 +122,7 @@ struct DispatchArgs {
   int64_t row_bytes;           // 2H (bf16) or H (fp8)
   int32_t scale_row_bytes;     // (H/128)*4 or 0
   int32_t scale_pitch;         // bytes between scale rows of a region (>= scale_row_bytes)
+  int32_t scales16;            // scale rows move in 16-byte pieces, at most 1 KiB of them
   int32_t k;
   int32_t L;                   // experts per rank
   const int32_t* topk_idx;
@@ -141,6 +142,8 @@ struct DispatchArgs {
   int32_t trace_waves;
 };
 
+// MOE_POLICY_BALANCED without a wavefront count or a trace takes the unit
+// kernel, everything else the explicit splits.
 hipError_t launch_dispatch(const DispatchArgs& a, int policy, hipStream_t stream);
 
 struct CombineArgs {
