@@ -655,11 +655,27 @@ __global__ __launch_bounds__(kBlock) void layout_place_kernel(
   }
 
   if (FIXED) {
-    // Window rows no slot fills have no source: for the experts this chunk
-    // owns (e = c, c + nc, ...), rows [e*C + placed_e, (e+1)*C).
-    for (int e = c; e < E; e += nc) {
-      const int placed = eoff[e + 1] - eoff[e];
-      for (int i = placed + tid; i < C; i += kBlock) row_src[(int64_t)e * C + i] = -1;
+    // Window rows no slot fills have no source: rows [e*C + placed_e,
+    // (e+1)*C) of every expert, all window rows strided over the grid's
+    // threads (window and row within it stepped without a division).  A loop
+    // over experts, one workgroup-wide pass each, took 27 us for 256 windows
+    // of 16 rows in the one-workgroup layout.
+    if (C > 0) {
+      const int stride = nc * kBlock, n_rows = E * C;
+      const int de = stride / C, dw = stride - de * C;
+      int i = c * kBlock + tid;
+      int e = i / C, in = i - e * C;
+      while (i < n_rows) {
+        if (in >= eoff[e + 1] - eoff[e]) row_src[i] = -1;
+        if (i > n_rows - stride) break;   // no sum past 2^31
+        i += stride;
+        e += de;
+        in += dw;
+        if (in >= C) {
+          in -= C;
+          ++e;
+        }
+      }
     }
   } else {
     // Rows past the last routed slot have no source.
