@@ -26,10 +26,10 @@
  *    and caches no memory (moe_layout_scratch uses one fixed array of the
  *    library's, see there).  Host-side it keeps only what it reads once per
  *    device (device properties, that array's address).  Device-side, the
- *    default work split of moe_dispatch / moe_combine hands parts out from
- *    ticket counters in the caller's workspace, which every call leaves at
- *    zero: calls that share a workspace must not overlap in time; separate
- *    workspaces are independent.
+ *    explicit splits of moe_dispatch_ex / moe_combine_ex may hand parts out
+ *    from ticket counters in the caller's workspace, which every call leaves
+ *    at zero, and the layouts rewrite the workspace: such calls that share a
+ *    workspace must not overlap in time; separate workspaces are independent.
  *  - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *    Every call only enqueues kernels on `stream` and returns without
  *    synchronizing; outputs are ready when the stream reaches that point.
@@ -62,7 +62,7 @@
  *    range.  The environment variable MOE_LAYOUT_SYNC_LIMIT_US, read once
  *    per device, replaces the 2 s limit; tests use it to reach this path).
  *  - The three calls of one batch must see the same topk_idx, T, k, E, R and
- *    workspace; dispatch and combine read the partition plan that moe_layout
+ *    workspace; the explicit splits read the partition plan that moe_layout
  *    leaves in the workspace.
  */
 #ifndef MOE_H_
@@ -96,8 +96,8 @@ extern "C" {
 #define MOE_FP8_BLOCK 128
 
 /* Number of parts P of the byte-balanced partition plan (parts of equal byte
- * cost), for the explicit splits of moe_dispatch_ex / moe_combine_ex, the
- * expansion and the partial combine of the per-peer path.  They launch W
+ * cost), for the explicit splits of moe_dispatch_ex / moe_combine_ex, which
+ * launch W
  * wavefronts, W a power of two that divides P, sized from the bytes each
  * wavefront keeps in flight.  Wavefront g starts at part g; later parts are
  * either strided statically (g+W, g+2W, ...) or handed out at run time in
@@ -248,10 +248,7 @@ int moe_layout_fixed(const int32_t* topk_idx, int64_t T, int k, int E, int R, in
  *           wavefronts write partially; packed 224-byte rows cost ~30 us more
  *           per 131k rows on MI355X.
  * recv_cap  [R] int32 capacity of each region in rows.
- * topk_idx, pos, rank_offset, workspace: as produced by moe_layout.  Batches
- *           of more than 2^24 (token, KiB of row) units take the plan's parts
- *           with tickets in the workspace: two such dispatch calls that share
- *           a workspace must not run at the same time on different streams.
+ * topk_idx, pos, rank_offset, workspace: as produced by moe_layout.
  * Bytes of a region beyond the rows dispatch writes are left untouched.
  */
 int moe_dispatch(const void* x, const float* x_scales, int dtype, int64_t T, int H,
@@ -265,8 +262,8 @@ int moe_dispatch(const void* x, const float* x_scales, int dtype, int64_t T, int
  * bit-identical regions and identical y). */
 #define MOE_POLICY_BALANCED 0 /* the library's choice (moe_dispatch, moe_combine): one
                                * wavefront per token and KiB of row.  With a
-                               * wavefront count or a trace, and for more than 2^24
-                               * such units, byte-balanced parts of the plan: when a
+                               * wavefront count or a trace, byte-balanced parts of
+                               * the plan: when a
                                * part carries 64 KiB (dispatch) or 128 KiB (combine)
                                * or more on average, every part after each
                                * wavefront's first is handed out at run time;
@@ -334,11 +331,7 @@ int moe_dispatch_ex(const void* x, const float* x_scales, int dtype, int64_t T, 
  * expert_y  [R] uint64 bf16 region bases (device table), 16-byte aligned.
  * topk_w    [T,k] float32.
  * y         [T,H] bf16 output, 16-byte aligned, 2H a multiple of 16.
- * workspace as produced by moe_layout.  Batches of more than 2^24 (token,
- *           KiB of row) units take the plan's parts with tickets in the
- *           workspace (separate from dispatch's): two such combine calls that
- *           share a workspace must not run at the same time on different
- *           streams.
+ * workspace as produced by moe_layout.
  */
 int moe_combine(const uint64_t* expert_y, const float* topk_w, int64_t T, int H, int k,
                 int E, int R, const int32_t* topk_idx, const int32_t* pos,
@@ -397,8 +390,8 @@ int moe_layout_dedup_workspace_bytes(int64_t T, int k, int E, int R, size_t* out
  *      workspace          pair-row plan (see above) plus internal scratch,
  *                         moe_layout_dedup_workspace_bytes, 256-byte aligned.
  * A separate workspace from moe_layout's: the per-slot calls (moe_expand,
- * moe_combine_local) read moe_layout's plan, the pair-row calls
- * (moe_dispatch_dedup, moe_combine_dedup) read this one.
+ * moe_combine_local) take moe_layout's, the pair-row calls
+ * (moe_dispatch_dedup, moe_combine_dedup) this one.
  */
 int moe_layout_dedup(const int32_t* topk_idx, int64_t T, int k, int E, int R, int32_t* tok_count,
                      int32_t* tok_offset, int32_t* tok_pos, int32_t* tok_src, void* workspace,
@@ -432,7 +425,7 @@ int moe_dispatch_dedup(const void* x, const float* x_scales, int dtype, int64_t 
  *     moe_dispatch_dedup (scale rows scale_pitch bytes apart in both);
  * recv_x / recv_scales / recv_cap: expert-ordered regions as for
  *     moe_dispatch;
- * pos, rank_offset, workspace: from moe_layout (its plan splits the work);
+ * pos, rank_offset, workspace: from moe_layout;
  * tok_pos, tok_offset: from moe_layout_dedup.
  * A pair row at or past dedup_cap[r], or a destination at or past
  * recv_cap[r], is skipped and sets MOE_STATUS_CAPACITY.  Other errors as

@@ -432,6 +432,7 @@ int moe_expand(const uint64_t* dedup_x, const uint64_t* dedup_scales, int dtype,
   a.row_bytes = row_bytes;
   a.scale_row_bytes = scale_row;
   a.scale_pitch = fp8 ? pitch : 0;
+  a.scales16 = fp8 && scale_row % 16 == 0 && pitch % 16 == 0 && pitch <= moe::kWaveBytes;
   a.k = k;
   a.L = E / R;
   a.topk_idx = topk_idx;
@@ -439,10 +440,6 @@ int moe_expand(const uint64_t* dedup_x, const uint64_t* dedup_scales, int dtype,
   a.rank_offset = rank_offset;
   a.tok_pos = tok_pos;
   a.tok_offset = tok_offset;
-  a.bound = static_cast<const int32_t*>(workspace);
-  a.tickets = reinterpret_cast<uint32_t*>(static_cast<char*>(const_cast<void*>(workspace)) +
-                                          moe::layout_geom(T, E).ticket_offset) +
-              2 * moe::kTicketGroupWords;
   a.status = status;
   a.R = R;
   return launched(moe::launch_expand(a, as_stream(stream)));
@@ -479,7 +476,6 @@ int moe_combine_local(const uint64_t* expert_y, const float* topk_w, int64_t T, 
   a.rank_offset = rank_offset;
   a.tok_pos = tok_pos;
   a.tok_offset = tok_offset;
-  a.bound = static_cast<const int32_t*>(workspace);
   a.status = status;
   a.tokens = T;
   a.R = R;

@@ -10,8 +10,7 @@
 // touched once.
 //
 // Explicit splits (combine_kernel; moe_combine_ex with a policy, a wavefront
-// count or a trace, and batches of more units than one grid holds):
-// persistent wavefronts over the byte-balanced plan (wavefront g of W takes
+// count or a trace): persistent wavefronts over the byte-balanced plan (wavefront g of W takes
 // parts g, g + W, ... or claims them at run time).  Slot metadata for a batch
 // of 64/k tokens is resolved once, one slot per lane, and parked in LDS; for
 // each token the wavefront walks the output row in 1 KiB segments, the next
@@ -26,35 +25,12 @@
 namespace moe {
 namespace {
 
-__device__ __forceinline__ void fma8(float (&acc)[8], const u32x4& v, float w) {
-  acc[0] = __builtin_fmaf(w, bf16_lo(v.x), acc[0]);
-  acc[1] = __builtin_fmaf(w, bf16_hi(v.x), acc[1]);
-  acc[2] = __builtin_fmaf(w, bf16_lo(v.y), acc[2]);
-  acc[3] = __builtin_fmaf(w, bf16_hi(v.y), acc[3]);
-  acc[4] = __builtin_fmaf(w, bf16_lo(v.z), acc[4]);
-  acc[5] = __builtin_fmaf(w, bf16_hi(v.z), acc[5]);
-  acc[6] = __builtin_fmaf(w, bf16_lo(v.w), acc[6]);
-  acc[7] = __builtin_fmaf(w, bf16_hi(v.w), acc[7]);
-}
-
-__device__ __forceinline__ u32x4 pack8(const float (&acc)[8]) {
-  u32x4 o;
-  o.x = pack_bf16x2(acc[0], acc[1]);
-  o.y = pack_bf16x2(acc[2], acc[3]);
-  o.z = pack_bf16x2(acc[4], acc[5]);
-  o.w = pack_bf16x2(acc[6], acc[7]);
-  return o;
-}
-
 template <int KW>
 __device__ __forceinline__ void gather(u32x4 (&v)[KW], const uint8_t* const (&src)[KW],
                                        uint32_t off) {
 #pragma unroll
   for (int j = 0; j < KW; ++j) v[j] = ld16_stream(src[j] + off);
 }
-
-// Buffer-resource loads (Rsrc) with cache policy 2, the non-temporal hint.
-constexpr int kLoadNonTemporal = 2;
 
 // Weighted sum of one 1 KiB segment.  MASKED: unused slots read a routed
 // row of the same token; their data is zeroed (bitwise, so an Inf or NaN
@@ -308,7 +284,7 @@ hipError_t launch_dyn(const CombineArgs& a, int64_t in_flight, hipStream_t strea
 //
 // Bound by HBM reads (k gathers per store).  As in dispatch the number of
 // bytes in flight over the chip sets the rate, from both sides, so the launch
-// limits the resident wavefronts (combine_unit_waves) and a slice is as
+// limits the resident wavefronts (gather_unit_waves) and a slice is as
 // narrow as keeps a few gathers in flight per wavefront: S = 1 from k = 3,
 // at most 2 for k = 2 and 4 for k = 1 (16384 x 14 KiB on MI355X, us at S = 1 / 2 / 4:
 // k = 1 120 87 84, k = 2 133 118 119, k = 4 192 196 201, k = 8 340 360 360).
@@ -326,12 +302,12 @@ hipError_t launch_dyn(const CombineArgs& a, int64_t in_flight, hipStream_t strea
 //   16384 x 14 KiB, k = 1, uniform            104 -> 80  (5850)
 //   512 x 14 KiB, k = 8                       25.7 -> 13.0
 template <int KB, int S>
-__global__ __launch_bounds__(kBlock) void combine_unit_kernel(CombineArgs a, int slices,
-                                                              int units) {
+__global__ __launch_bounds__(kBlock) void combine_unit_kernel(CombineArgs a, int first,
+                                                              int slices, int units) {
   const int lane = threadIdx.x & (kWave - 1);
   const int u = uniform(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave);
   if (u >= units) return;
-  const int t = u / slices, q = u - t * slices;
+  const int q = u % slices, t = first + u / slices;
   const uint32_t rb = (uint32_t)a.row_bytes;
   const int k = a.k;
   const uint32_t o0 = (uint32_t)q * (S * kWaveBytes) + lane * kVecBytes;
@@ -399,27 +375,16 @@ __global__ __launch_bounds__(kBlock) void combine_unit_kernel(CombineArgs a, int
   }
 }
 
-// Resident wavefronts per compute unit: about 160 KiB of gathers in flight,
-// at least 16 wavefronts.  Measured on MI355X (us at 32 / 28 / 24 / 20 / 16 /
-// 12 wavefronts): k = 8 Zipf, 14 KiB rows 369 - 354 340 337 342; k = 8 Zipf,
-// 8 KiB rows 422 - 409 391 391 414; k = 6 198 196 197 201 207 -; k = 4 192 194
-// 199 208 221 -; k = 16 342 342 343 342 338 355; k = 8, 512 B rows 28.3 29.2
-// 30.4 32.3 34.9 46.
-int combine_unit_waves(int64_t wave_bytes) {
-  const int64_t w = ((160ll << 10) / wave_bytes + 3) / 4 * 4;
-  return w < 16 ? 16 : w > 32 ? 32 : (int)w;
-}
-
 template <int KB, int S>
 hipError_t launch_unit_as(const CombineArgs& a, hipStream_t stream) {
   const int slices = (int)((row_slices(a.row_bytes) + S - 1) / S);
-  const int units = (int)a.tokens * slices;
   const int64_t width = a.row_bytes < S * kWaveBytes ? a.row_bytes : S * kWaveBytes;
-  hipLaunchKernelGGL((combine_unit_kernel<KB, S>),
-                     dim3((units + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock),
-                     wave_limit_lds(combine_unit_waves(a.k * width), kWavesPerBlock), stream, a,
-                     slices, units);
-  return hipGetLastError();
+  const unsigned lds = wave_limit_lds(gather_unit_waves(a.k * width), kWavesPerBlock);
+  return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
+    hipLaunchKernelGGL((combine_unit_kernel<KB, S>),
+                       dim3((units + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), lds,
+                       stream, a, first, slices, units);
+  });
 }
 
 template <int KB>
@@ -445,8 +410,7 @@ hipError_t launch_units(const CombineArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_combine(const CombineArgs& a, int policy, hipStream_t stream) {
-  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace &&
-      a.tokens * row_slices(a.row_bytes) <= kMaxUnits)
+  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace)
     return launch_units(a, stream);
   const bool large = claim_all_parts(a.tokens, a.row_bytes, a.k);
   const bool claim = policy == MOE_POLICY_DYNAMIC || (policy == MOE_POLICY_BALANCED && large);

@@ -31,6 +31,7 @@ struct ExpandArgs {
   int64_t row_bytes;
   int32_t scale_row_bytes;
   int32_t scale_pitch;
+  int32_t scales16;              // scale rows move in 16-byte pieces, at most 1 KiB of them
   int32_t k;
   int32_t L;
   const int32_t* topk_idx;
@@ -38,8 +39,6 @@ struct ExpandArgs {
   const int32_t* rank_offset;
   const int32_t* tok_pos;
   const int32_t* tok_offset;
-  const int32_t* bound;          // plan of the per-slot layout
-  uint32_t* tickets;             // claimed parts: {next, done}, zeroed by the layout
   uint32_t* status;
   int32_t R;                     // ranks
 };
@@ -60,7 +59,6 @@ struct LocalArgs {
   const int32_t* rank_offset;
   const int32_t* tok_pos;
   const int32_t* tok_offset;
-  const int32_t* bound;          // plan of the per-slot layout
   uint32_t* status;
   int64_t tokens;                // T
   int32_t R;                     // ranks

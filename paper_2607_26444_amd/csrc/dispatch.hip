@@ -12,8 +12,7 @@
 // the chip by its slices.
 //
 // Explicit splits (dispatch_kernel; moe_dispatch_ex with a policy, a
-// wavefront count or a trace, and batches of more units than one grid holds):
-// persistent wavefronts over the byte-balanced plan (Section 6.2 with one
+// wavefront count or a trace): persistent wavefronts over the byte-balanced plan (Section 6.2 with one
 // memory tier, Appendix D third level).  moe_layout leaves MOE_PLAN_PARTS
 // contiguous token ranges of equal byte cost; wavefront g of W takes parts g,
 // g + W, g + 2W, ... or claims parts in plan order at run time.  A wavefront
@@ -238,12 +237,12 @@ __device__ __forceinline__ void store16(void* p, u32x4 v) {
 // groups of `pieces` lanes, one group per destination, so one store
 // instruction writes 64 / pieces scale rows whole.
 template <bool SCALES, bool NT>
-__global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, int slices,
-                                                               int units) {
+__global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, int first,
+                                                               int slices, int units) {
   const int lane = threadIdx.x & (kWave - 1);
   const int u = uniform(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
   if (u >= units) return;
-  const int t = u / slices, q = u - t * slices;
+  const int q = u % slices, t = first + u / slices;
   const uint32_t rb = (uint32_t)a.row_bytes;
   const uint32_t sb = (uint32_t)a.scale_row_bytes;
   const uint32_t sp = (uint32_t)a.scale_pitch;
@@ -348,23 +347,24 @@ constexpr int64_t kScaledStreamBytes = 768ll << 20;
 template <bool SCALES>
 hipError_t launch_unit(const DispatchArgs& a, hipStream_t stream) {
   const int slices = (int)row_slices(a.row_bytes);
-  const int units = (int)a.tokens * slices;
   // One wavefront per workgroup frees its slot as soon as it is done.  With
   // scale rows the slice-0 wavefront lives longer, and workgroups of four
   // measured better at the same limit (fp8, 16384 x 7 KiB: uniform 219 -> 208
   // us, Zipf 202 -> 186).
   const int wpb = SCALES ? kWavesPerBlock : 1;
   const int64_t rows = a.rows_hint > 0 ? a.rows_hint : a.k;
-  const dim3 grid((units + wpb - 1) / wpb), block(wpb * kWave);
   const bool small_x = !SCALES && a.tokens * a.row_bytes <= (96ll << 20);
+  const bool stream_stores = !SCALES || a.tokens * rows * a.row_bytes <= kScaledStreamBytes;
   const unsigned lds = wave_limit_lds(dispatch_unit_waves(rows, small_x), wpb);
-  if (SCALES && a.tokens * rows * a.row_bytes > kScaledStreamBytes)
-    hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, !SCALES>), grid, block, lds, stream, a,
-                       slices, units);
-  else
-    hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true>), grid, block, lds, stream, a, slices,
-                       units);
-  return hipGetLastError();
+  return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
+    const dim3 grid((units + wpb - 1) / wpb), block(wpb * kWave);
+    if (stream_stores)
+      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true>), grid, block, lds, stream, a, first,
+                         slices, units);
+    else
+      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, !SCALES>), grid, block, lds, stream, a,
+                         first, slices, units);
+  });
 }
 
 // Pull dispatch for the partitioning study: a wavefront walks a range of
@@ -562,8 +562,7 @@ hipError_t launch_scales(const DispatchArgs& a, int policy, hipStream_t stream) 
 }  // namespace
 
 hipError_t launch_dispatch(const DispatchArgs& a, int policy, hipStream_t stream) {
-  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace &&
-      a.tokens * row_slices(a.row_bytes) <= kMaxUnits)
+  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace)
     return a.x_scales ? launch_unit<true>(a, stream) : launch_unit<false>(a, stream);
   return a.x_scales ? launch_scales<true>(a, policy, stream)
                     : launch_scales<false>(a, policy, stream);

@@ -94,8 +94,20 @@ __host__ __forceinline__ bool claim_all_parts(int64_t tokens, int64_t row_bytes,
 __host__ __forceinline__ int64_t row_slices(int64_t row_bytes) {
   return (row_bytes + kWaveBytes - 1) / kWaveBytes;
 }
-// Units one launch takes: a grid holds fewer than 2^32 work items in x.
+// Units one launch takes (a grid holds fewer than 2^32 work items in x);
+// larger batches are launched in several token ranges.
 constexpr int64_t kMaxUnits = 1 << 24;
+template <typename F>
+__host__ hipError_t launch_token_ranges(int64_t tokens, int slices, F&& launch) {
+  const int64_t step = kMaxUnits / slices > 0 ? kMaxUnits / slices : 1;
+  for (int64_t t = 0; t < tokens; t += step) {
+    const int64_t n = tokens - t < step ? tokens - t : step;
+    launch((int)t, (int)(n * slices));
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
+}
 
 // Dynamic LDS that keeps at most `waves` wavefronts of a kernel with
 // wpb-wavefront workgroups (and no LDS of its own) resident on a compute
@@ -104,6 +116,18 @@ constexpr int64_t kMaxUnits = 1 << 24;
 __host__ __forceinline__ unsigned wave_limit_lds(int waves, int wpb) {
   const int blocks = waves / wpb > 0 ? waves / wpb : 1;
   return blocks * wpb >= 32 ? 0u : (unsigned)(128 / blocks * 1280);
+}
+
+// Resident wavefronts per compute unit of the gathering unit kernels
+// (combine, partial combine), wave_bytes gathered per wavefront: about 160 KiB
+// in flight, at least 16 wavefronts.  Combine on MI355X (us at 32 / 28 / 24 /
+// 20 / 16 / 12 wavefronts): k = 8 Zipf, 14 KiB rows 369 - 354 340 337 342; k =
+// 8 Zipf, 8 KiB rows 422 - 409 391 391 414; k = 6 198 196 197 201 207 -; k = 4
+// 192 194 199 208 221 -; k = 16 342 342 343 342 338 355; k = 8, 512 B rows
+// 28.3 29.2 30.4 32.3 34.9 46.
+__host__ __forceinline__ int gather_unit_waves(int64_t wave_bytes) {
+  const int64_t w = ((160ll << 10) / wave_bytes + 3) / 4 * 4;
+  return w < 16 ? 16 : w > 32 ? 32 : (int)w;
 }
 
 // fixed_cap < 0: packed layout; >= 0: fixed windows of fixed_cap rows.
@@ -168,7 +192,7 @@ struct CombineArgs {
 };
 
 // MOE_POLICY_BALANCED without a wavefront count or a trace takes the unit
-// kernel, everything else the persistent split.
+// kernel, everything else the explicit splits.
 hipError_t launch_combine(const CombineArgs& a, int policy, hipStream_t stream);
 
 struct ExpertArgs {
@@ -209,8 +233,7 @@ __device__ __forceinline__ u32x4 ld16_stream(const void* p) {
 __device__ __forceinline__ void st16_stream(void* p, u32x4 v) {
   __builtin_nontemporal_store(v, (gu32x4*)(uintptr_t)p);
 }
-// Row stores of the copy kernels (dispatch, expand), VPL KiB per pass:
-// non-temporal for rows of more than 8 KiB, ordinary for narrower rows.
+// Row stores of the persistent dispatch, VPL KiB per pass: non-temporal for rows of more than 8 KiB, ordinary for narrower rows.
 // Measured in whole steps on MI355X: non-temporal stores are 8-12% faster
 // for dispatch's 14 KiB rows (prefill, decode), ordinary stores 4% faster
 // for the fp8 workload's 7 KiB rows (211 vs 220 us) and 2.5% for the 8 KiB
@@ -233,6 +256,8 @@ __device__ __forceinline__ void st4(void* p, uint32_t v) { *(gu32*)(uintptr_t)p 
 // on gfx9-family GPUs.
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 constexpr int kRsrcWord3 = 0x00020000;
+// Cache policy of a buffer load: the non-temporal hint.
+constexpr int kLoadNonTemporal = 2;
 
 // Wavefront-uniform value held in a scalar register.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -249,7 +274,7 @@ __device__ __forceinline__ float readlane_f32(float v, int l) {
 }
 
 // Work tickets.  Each copy kernel that hands parts out at run time (dispatch,
-// combine, expand) has a group of kTicketShards counters, each {next claim,
+// combine) has a group of kTicketShards counters, each {next claim,
 // wavefronts done} on its own 128-byte line; group k starts at word
 // k * kTicketGroupWords of the ticket block.  On MI355X device-scope atomics
 // on one address serialize at ~13 ns each: one counter for all wavefronts
@@ -287,7 +312,7 @@ __device__ __forceinline__ int waves_in_shard(int s, int W) {
   return n;
 }
 constexpr int kTicketGroupWords = 16 * kTicketStride;              // 2 KiB per kernel (<= 16 shards)
-constexpr int kTicketGroups = 3;                                   // dispatch, combine, expand
+constexpr int kTicketGroups = 3;                                   // dispatch, combine, one spare
 constexpr size_t kTicketBlockBytes = 8192;                         // groups + generation word
 static_assert(kTicketGroups * kTicketGroupWords * 4 + 128 <= (int)kTicketBlockBytes, "tickets");
 
@@ -416,6 +441,27 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   __bf16 a = (__bf16)lo, b = (__bf16)hi;
   return (uint32_t)__builtin_bit_cast(uint16_t, a) |
          ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+}
+
+// acc += w * (8 bf16 values), and 8 sums rounded to bf16.
+__device__ __forceinline__ void fma8(float (&acc)[8], const u32x4& v, float w) {
+  acc[0] = __builtin_fmaf(w, bf16_lo(v.x), acc[0]);
+  acc[1] = __builtin_fmaf(w, bf16_hi(v.x), acc[1]);
+  acc[2] = __builtin_fmaf(w, bf16_lo(v.y), acc[2]);
+  acc[3] = __builtin_fmaf(w, bf16_hi(v.y), acc[3]);
+  acc[4] = __builtin_fmaf(w, bf16_lo(v.z), acc[4]);
+  acc[5] = __builtin_fmaf(w, bf16_hi(v.z), acc[5]);
+  acc[6] = __builtin_fmaf(w, bf16_lo(v.w), acc[6]);
+  acc[7] = __builtin_fmaf(w, bf16_hi(v.w), acc[7]);
+}
+
+__device__ __forceinline__ u32x4 pack8(const float (&acc)[8]) {
+  u32x4 o;
+  o.x = pack_bf16x2(acc[0], acc[1]);
+  o.y = pack_bf16x2(acc[2], acc[3]);
+  o.z = pack_bf16x2(acc[4], acc[5]);
+  o.w = pack_bf16x2(acc[6], acc[7]);
+  return o;
 }
 
 }  // namespace moe

@@ -66,3 +66,26 @@ def test_units_match_oracle_and_persistent_split(T, H, E, R, k, payload, mask, s
                      combine_policy=moe.MOE_POLICY_STATIC)
     assert np.array_equal(run.y, again.y)
     assert run.layout["status"] == again.layout["status"]
+
+
+def test_more_units_than_one_launch():
+    """2^24 + 5 one-slice tokens: the units go out in two launches.  k = 1 and
+    unit weights, so y is x bit for bit and every region row is its token's."""
+    from paper_2607_26444_amd import moe
+    T, H, E, R = (1 << 24) + 5, 8, 4, 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    idx = torch.randint(0, E, (T, 1), generator=g, device="cuda", dtype=torch.int32)
+    x = torch.randn(T, H, generator=g, device="cuda").to(torch.bfloat16)
+    lay = moe.Layout(T, 1, E, R)
+    lay.run(idx)
+    reg = moe.Regions(lay.rank_count.tolist(), 2 * H, fill=0)
+    moe.moe_dispatch(x, None, moe.MOE_DTYPE_BF16, H, E, R, idx, lay.pos, lay.rank_offset,
+                     reg.table, None, reg.cap, lay.workspace, lay.status)
+    rows = torch.cat([reg.region(r).view(torch.bfloat16) for r in range(R)])
+    assert torch.equal(rows, x[lay.row_src.long()])
+    y = torch.zeros_like(x)
+    moe.moe_combine(reg.table, torch.ones(T, 1, device="cuda"), H, E, R, idx, lay.pos,
+                    lay.rank_offset, reg.cap, y, lay.workspace, lay.status)
+    assert torch.equal(y, x)
+    assert int(lay.status) == 0
