@@ -293,21 +293,46 @@ hipError_t launch_dyn(const CombineArgs& a, int64_t in_flight, hipStream_t strea
 // memory, and so does the part of a slice past the row's end.  Measured on
 // MI355X against the persistent split below (us before -> after, GB/s of
 // algorithmic bytes after):
-//   16384 x 14 KiB, k = 8, Zipf 1.2 routing   366 -> 340  (6220)
-//   32768 x 8 KiB, k = 8, Zipf 1.5            431 -> 391  (6180)
+//   16384 x 14 KiB, k = 8, Zipf 1.2 routing   366 -> 334  (6330)
+//   32768 x 8 KiB, k = 8, Zipf 1.5            431 -> 392  (6160)
 //   8192 x 14 KiB, k = 16, uniform            444 -> 338  (5900)
 //   16384 x 10 KiB, k = 6, uniform            221 -> 196  (5990)
 //   4096 x 14 KiB, k = 8, uniform             90.3 -> 88.0 (6010)
 //   32768 x 512 B, k = 8                      44.4 -> 28.3 (5340)
 //   16384 x 14 KiB, k = 1, uniform            104 -> 80  (5850)
 //   512 x 14 KiB, k = 8                       25.7 -> 13.0
+//
+// group > 0: tokens go to the XCDs in groups of that many neighbours
+// (workgroups are placed on the eight XCDs in turn), so one XCD's L2 fetches
+// a group's slot metadata once, instead of every XCD fetching the line for
+// its few slices.  Groups of 4 (k = 8: one 128-byte line of each array)
+// measured 16384 x 14 KiB Zipf 342 -> 334 us, uniform 358 -> 352, 32768 x 8
+// KiB Zipf 405 -> 392, 4096 x 14 KiB 88.2 -> 87.9; 1 and 2 gain half to two
+// thirds of that.  Dispatch, whose rows want to be written by all XCDs at
+// once, got 2-16% slower that way and the partial combine did not change.
+constexpr int kXcds = 8;
+constexpr int kXcdGroup = 4;
 template <int KB, int S>
 __global__ __launch_bounds__(kBlock) void combine_unit_kernel(CombineArgs a, int first,
-                                                              int slices, int units) {
+                                                              int slices, int units,
+                                                              int group) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int u = uniform(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave);
-  if (u >= units) return;
-  const int q = u % slices, t = first + u / slices;
+  int q, t;
+  if (group > 0) {
+    // workgroup b runs on XCD b % kXcds: unit `u` of that XCD's own sequence
+    const int x = blockIdx.x % kXcds;
+    const int u = uniform(blockIdx.x / kXcds * kWavesPerBlock + threadIdx.x / kWave);
+    const int n = u / slices;   // n-th token of this XCD
+    q = u % slices;
+    t = (n / group * kXcds + x) * group + n % group;
+    if (t >= units / slices) return;
+  } else {
+    const int u = uniform(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave);
+    if (u >= units) return;
+    q = u % slices;
+    t = u / slices;
+  }
+  t += first;
   const uint32_t rb = (uint32_t)a.row_bytes;
   const int k = a.k;
   const uint32_t o0 = (uint32_t)q * (S * kWaveBytes) + lane * kVecBytes;
@@ -381,9 +406,13 @@ hipError_t launch_unit_as(const CombineArgs& a, hipStream_t stream) {
   const int64_t width = a.row_bytes < S * kWaveBytes ? a.row_bytes : S * kWaveBytes;
   const unsigned lds = wave_limit_lds(gather_unit_waves(a.k * width), kWavesPerBlock);
   return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
+    // Batches of a few tokens spread every token's slices over the XCDs.
+    const int tokens = units / slices, round = kXcds * kXcdGroup;
+    const int group = tokens >= 8 * round ? kXcdGroup : 0;
+    const int64_t launched = group ? (int64_t)(tokens + round - 1) / round * round * slices : units;
     hipLaunchKernelGGL((combine_unit_kernel<KB, S>),
-                       dim3((units + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), lds,
-                       stream, a, first, slices, units);
+                       dim3((launched + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), lds,
+                       stream, a, first, slices, units, group);
   });
 }
 
