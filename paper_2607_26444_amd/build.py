@@ -1,4 +1,5 @@
-"""Build libmoe.so (HIP, gfx950) in-tree with hipcc.
+"""Build libmoe.so (HIP, gfx950) in-tree with hipcc, and _moecall.so, the
+native argument marshalling of the Python binding, with the host compiler.
 
 python -m paper_2607_26444_amd.build [--isa DIR]
 
@@ -12,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +21,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libmoe.so")
+PYCALL = os.path.join(HERE, "_moecall.so")
 SOURCES = ["api.hip", "layout.hip", "dispatch.hip", "combine.hip", "expert.hip", "dedup.hip",
            "scratch.hip"]
 
@@ -48,6 +51,17 @@ def _compile(args):
     return obj
 
 
+def build_pycall(verbose: bool = False) -> str:
+    cmd = [os.environ.get("CXX") or shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC",
+           "-Wall", "-shared", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "pycall.cpp"), "-ldl", "-o", PYCALL + ".tmp"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(PYCALL + ".tmp", PYCALL)
+    return PYCALL
+
+
 def build(isa_dir: str | None = None, verbose: bool = False) -> str:
     with tempfile.TemporaryDirectory() as tmp:
         work = isa_dir or tmp
@@ -61,6 +75,7 @@ def build(isa_dir: str | None = None, verbose: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
         os.replace(tmp_lib, LIB)
+    build_pycall(verbose)
     return LIB
 
 

@@ -2,9 +2,11 @@
 
 Argument marshalling only: every function passes device pointers of torch
 tensors and the current HIP stream to the C entry point of the same name;
-all work runs in the library's kernels.  torch is imported before the
-library is loaded so that both use the one HIP runtime already in the
-process.  There is no fallback: without libmoe.so every call raises.
+all work runs in the library's kernels.  The calls of a batch go through the
+native marshalling of csrc/pycall.cpp, the others through ctypes.  torch is
+imported before the library is loaded so that both use the one HIP runtime
+already in the process.  There is no fallback: without libmoe.so and
+_moecall.so every call raises.
 """
 from __future__ import annotations
 
@@ -111,6 +113,26 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_fast = None
+
+
+def _calls():
+    """The native marshalling (_moecall.so), bound to the loaded library."""
+    global _fast
+    if _fast is None:
+        lib()
+        try:
+            from . import _moecall
+        except ImportError as e:
+            raise RuntimeError(
+                f"{os.path.join(HERE, '_moecall.so')} cannot be loaded: build it with "
+                "`python -m paper_2607_26444_amd.build` (no fallback exists)") from e
+        _moecall.init(LIB_PATH, ctypes.ArgumentError, torch._C._cuda_getDevice,
+                      torch._C._cuda_getCurrentRawStream)
+        _fast = _moecall
+    return _fast
+
+
 def _ptr(t):
     if t is None:
         return None
@@ -148,11 +170,11 @@ def moe_layout_workspace_bytes(T: int, k: int, E: int, R: int) -> int:
 
 def moe_layout(topk_idx, E, R, expert_count, expert_offset, rank_count, rank_offset,
                pos, row_src, workspace, status, stream=None):
-    T, k = topk_idx.shape
-    _check("moe_layout", lib().moe_layout(
-        _ptr(topk_idx), T, k, E, R, _ptr(expert_count), _ptr(expert_offset),
-        _ptr(rank_count), _ptr(rank_offset), _ptr(pos), _ptr(row_src), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _ptr(status), _stream(stream)))
+    rc = (_fast or _calls()).layout(
+        topk_idx, E, R, expert_count, expert_offset, rank_count, rank_offset, pos, row_src,
+        workspace, status, stream)
+    if rc:
+        _check("moe_layout", rc)
 
 
 class DeviceBuffer:
@@ -189,21 +211,20 @@ def moe_layout_scratch(topk_idx, E, R, expert_count, expert_offset, rank_count, 
 
 def moe_layout_fixed(topk_idx, E, R, capacity, expert_count, expert_offset, rank_count,
                      rank_offset, pos, row_src, workspace, status, stream=None):
-    T, k = topk_idx.shape
-    _check("moe_layout_fixed", lib().moe_layout_fixed(
-        _ptr(topk_idx), T, k, E, R, capacity, _ptr(expert_count), _ptr(expert_offset),
-        _ptr(rank_count), _ptr(rank_offset), _ptr(pos), _ptr(row_src), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _ptr(status), _stream(stream)))
+    rc = (_fast or _calls()).layout_fixed(
+        topk_idx, E, R, capacity, expert_count, expert_offset, rank_count, rank_offset, pos,
+        row_src, workspace, status, stream)
+    if rc:
+        _check("moe_layout_fixed", rc)
 
 
 def moe_dispatch(x, x_scales, dtype, H, E, R, topk_idx, pos, rank_offset, recv_x,
                  recv_scales, recv_cap, workspace, status, stream=None, scale_pitch=0):
-    T, k = topk_idx.shape
-    _check("moe_dispatch", lib().moe_dispatch(
-        _ptr(x), _ptr(x_scales), dtype, T, H, k, E, R, _ptr(topk_idx), _ptr(pos),
-        _ptr(rank_offset), _ptr(recv_x), _ptr(recv_scales), scale_pitch, _ptr(recv_cap),
-        _ptr(workspace), workspace.numel() * workspace.element_size(), _ptr(status),
-        _stream(stream)))
+    rc = (_fast or _calls()).dispatch(
+        x, x_scales, dtype, H, E, R, topk_idx, pos, rank_offset, recv_x, recv_scales, recv_cap,
+        workspace, status, stream, scale_pitch)
+    if rc:
+        _check("moe_dispatch", rc)
 
 
 def moe_dispatch_ex(x, x_scales, dtype, H, E, R, topk_idx, pos, rank_offset, row_src,
@@ -231,11 +252,11 @@ def moe_combine_ex(expert_y, topk_w, H, E, R, topk_idx, pos, rank_offset, recv_c
 
 def moe_combine(expert_y, topk_w, H, E, R, topk_idx, pos, rank_offset, recv_cap, y,
                 workspace, status, stream=None):
-    T, k = topk_idx.shape
-    _check("moe_combine", lib().moe_combine(
-        _ptr(expert_y), _ptr(topk_w), T, H, k, E, R, _ptr(topk_idx), _ptr(pos),
-        _ptr(rank_offset), _ptr(recv_cap), _ptr(y), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _ptr(status), _stream(stream)))
+    rc = (_fast or _calls()).combine(
+        expert_y, topk_w, H, E, R, topk_idx, pos, rank_offset, recv_cap, y, workspace, status,
+        stream)
+    if rc:
+        _check("moe_combine", rc)
 
 
 def moe_expert_scale(recv_x, recv_scales, dtype, H, E, R, identity, expert_offset,
@@ -256,51 +277,46 @@ def moe_layout_dedup_workspace_bytes(T: int, k: int, E: int, R: int) -> int:
 
 def moe_layout_dedup(topk_idx, E, R, tok_count, tok_offset, tok_pos, tok_src, workspace,
                      status, stream=None):
-    T, k = topk_idx.shape
-    _check("moe_layout_dedup", lib().moe_layout_dedup(
-        _ptr(topk_idx), T, k, E, R, _ptr(tok_count), _ptr(tok_offset), _ptr(tok_pos),
-        _ptr(tok_src), _ptr(workspace), workspace.numel() * workspace.element_size(),
-        _ptr(status), _stream(stream)))
+    rc = (_fast or _calls()).layout_dedup(
+        topk_idx, E, R, tok_count, tok_offset, tok_pos, tok_src, workspace, status, stream)
+    if rc:
+        _check("moe_layout_dedup", rc)
 
 
 def moe_dispatch_dedup(x, x_scales, dtype, H, E, R, topk_idx, tok_pos, tok_offset, recv_x,
                        recv_scales, recv_cap, workspace, status, stream=None, scale_pitch=0):
-    T, k = topk_idx.shape
-    _check("moe_dispatch_dedup", lib().moe_dispatch_dedup(
-        _ptr(x), _ptr(x_scales), dtype, T, H, k, E, R, _ptr(topk_idx), _ptr(tok_pos),
-        _ptr(tok_offset), _ptr(recv_x), _ptr(recv_scales), scale_pitch, _ptr(recv_cap),
-        _ptr(workspace), workspace.numel() * workspace.element_size(), _ptr(status),
-        _stream(stream)))
+    rc = (_fast or _calls()).dispatch_dedup(
+        x, x_scales, dtype, H, E, R, topk_idx, tok_pos, tok_offset, recv_x, recv_scales, recv_cap,
+        workspace, status, stream, scale_pitch)
+    if rc:
+        _check("moe_dispatch_dedup", rc)
 
 
 def moe_expand(dedup_x, dedup_scales, dtype, H, E, R, topk_idx, pos, rank_offset, tok_pos,
                tok_offset, dedup_cap, recv_x, recv_scales, recv_cap, workspace, status,
                stream=None, scale_pitch=0):
-    T, k = topk_idx.shape
-    _check("moe_expand", lib().moe_expand(
-        _ptr(dedup_x), _ptr(dedup_scales), dtype, T, H, k, E, R, _ptr(topk_idx), _ptr(pos),
-        _ptr(rank_offset), _ptr(tok_pos), _ptr(tok_offset), _ptr(dedup_cap), _ptr(recv_x),
-        _ptr(recv_scales), scale_pitch, _ptr(recv_cap), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _ptr(status), _stream(stream)))
+    rc = (_fast or _calls()).expand(
+        dedup_x, dedup_scales, dtype, H, E, R, topk_idx, pos, rank_offset, tok_pos, tok_offset,
+        dedup_cap, recv_x, recv_scales, recv_cap, workspace, status, stream, scale_pitch)
+    if rc:
+        _check("moe_expand", rc)
 
 
 def moe_combine_local(expert_y, topk_w, H, E, R, topk_idx, pos, rank_offset, recv_cap,
                       tok_pos, tok_offset, part_cap, partial, workspace, status, stream=None):
-    T, k = topk_idx.shape
-    _check("moe_combine_local", lib().moe_combine_local(
-        _ptr(expert_y), _ptr(topk_w), T, H, k, E, R, _ptr(topk_idx), _ptr(pos),
-        _ptr(rank_offset), _ptr(recv_cap), _ptr(tok_pos), _ptr(tok_offset), _ptr(part_cap),
-        _ptr(partial), _ptr(workspace), workspace.numel() * workspace.element_size(),
-        _ptr(status), _stream(stream)))
+    rc = (_fast or _calls()).combine_local(
+        expert_y, topk_w, H, E, R, topk_idx, pos, rank_offset, recv_cap, tok_pos, tok_offset,
+        part_cap, partial, workspace, status, stream)
+    if rc:
+        _check("moe_combine_local", rc)
 
 
 def moe_combine_dedup(partial, H, E, R, topk_idx, tok_pos, tok_offset, part_cap, y, workspace,
                       status, stream=None):
-    T, k = topk_idx.shape
-    _check("moe_combine_dedup", lib().moe_combine_dedup(
-        _ptr(partial), T, H, k, E, R, _ptr(topk_idx), _ptr(tok_pos), _ptr(tok_offset),
-        _ptr(part_cap), _ptr(y), _ptr(workspace), workspace.numel() * workspace.element_size(),
-        _ptr(status), _stream(stream)))
+    rc = (_fast or _calls()).combine_dedup(
+        partial, H, E, R, topk_idx, tok_pos, tok_offset, part_cap, y, workspace, status, stream)
+    if rc:
+        _check("moe_combine_dedup", rc)
 
 
 # ------------------------------------------------------------ buffer plumbing
