@@ -236,7 +236,13 @@ __device__ __forceinline__ void store16(void* p, u32x4 v) {
 // in 16-byte multiples and at most 1 KiB, its pitched bytes are spread over
 // groups of `pieces` lanes, one group per destination, so one store
 // instruction writes 64 / pieces scale rows whole.
-template <bool SCALES, bool NT>
+//
+// SHIFT (rows_off_line): the slices of each destination row are cut at its
+// line boundaries, so a destination's bytes are loaded at an offset of its own,
+// KB destinations at a time, from the caches (us, persistent split -> this:
+// 16384 x 14352 B, k = 8, 470 -> 414; 8192 x 8208 B, k = 8, 129 -> 118; 4770 x
+// 6752 B, k = 6, 51 -> 43; 2000 x 12304 B, k = 4, 27 -> 22.6).
+template <bool SCALES, bool NT, bool SHIFT>
 __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, int first,
                                                                int slices, int units) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -254,7 +260,7 @@ __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, i
     e = a.topk_idx[(int64_t)t * k + lane];
   }
   u32x4 v = {0u, 0u, 0u, 0u}, sv = {0u, 0u, 0u, 0u};
-  if (off < rb) v = ld16(a.x + (int64_t)t * rb + off);
+  if (!SHIFT && off < rb) v = ld16(a.x + (int64_t)t * rb + off);
   const uint8_t* ssrc = SCALES ? a.x_scales + (int64_t)t * sb : nullptr;
   const bool scales_here = SCALES && q == 0;
   const int pieces = (int)sp / kVecBytes;
@@ -286,9 +292,30 @@ __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, i
       }
     }
   }
-  for (int j = 0; j < k; ++j) {
-    uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j));
-    if (d && off < rb) store16<NT>(d + off, v);
+  if constexpr (SHIFT) {
+    constexpr int KB = 8;
+    const Rsrc row = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(a.x + (int64_t)t * rb), (short)0, (int)rb, kRsrcWord3);
+    for (int j0 = 0; j0 < k; j0 += KB) {
+      u32x4 w[KB];
+#pragma unroll
+      for (int j = 0; j < KB; ++j) {
+        // before the row's start or past its end: nothing is read, nothing stored
+        const uint32_t o = off - ((uint32_t)readlane64(dst, j0 + j) & (kLine - 1));
+        w[j] = __builtin_amdgcn_raw_buffer_load_b128(row, o, 0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < KB; ++j) {
+        uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j0 + j));
+        const uint32_t o = off - ((uint32_t)(uintptr_t)d & (kLine - 1));
+        if (d && o < rb) store16<NT>(d + o, w[j]);
+      }
+    }
+  } else {
+    for (int j = 0; j < k; ++j) {
+      uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j));
+      if (d && off < rb) store16<NT>(d + off, v);
+    }
   }
   if (scales_here) {
     if (s16) {
@@ -346,24 +373,32 @@ constexpr int64_t kScaledStreamBytes = 768ll << 20;
 
 template <bool SCALES>
 hipError_t launch_unit(const DispatchArgs& a, hipStream_t stream) {
-  const int slices = (int)row_slices(a.row_bytes);
+  const int slices = unit_slices(a.row_bytes, 1);
   // One wavefront per workgroup frees its slot as soon as it is done.  With
   // scale rows the slice-0 wavefront lives longer, and workgroups of four
   // measured better at the same limit (fp8, 16384 x 7 KiB: uniform 219 -> 208
   // us, Zipf 202 -> 186).
-  const int wpb = SCALES ? kWavesPerBlock : 1;
+  const bool shift = !SCALES && rows_off_line(a.row_bytes);   // fp8 rows are whole lines
+  const int wpb = SCALES || shift ? kWavesPerBlock : 1;
   const int64_t rows = a.rows_hint > 0 ? a.rows_hint : a.k;
   const bool small_x = !SCALES && a.tokens * a.row_bytes <= (96ll << 20);
   const bool stream_stores = !SCALES || a.tokens * rows * a.row_bytes <= kScaledStreamBytes;
-  const unsigned lds = wave_limit_lds(dispatch_unit_waves(rows, small_x), wpb);
+  // Shifted slices load once per destination and want every wavefront (us at
+  // 32 / 20 / 12: 16384 x 14352 B, k = 8, 414 428 505; 16384 x 8240 B, k = 4,
+  // 155 173 201; 4770 x 6752 B, k = 6, 43 42 39).
+  const unsigned lds =
+      shift ? 0u : wave_limit_lds(dispatch_unit_waves(rows, small_x), wpb);
   return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
     const dim3 grid((units + wpb - 1) / wpb), block(wpb * kWave);
-    if (stream_stores)
-      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true>), grid, block, lds, stream, a, first,
-                         slices, units);
-    else
-      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, !SCALES>), grid, block, lds, stream, a,
+    if (shift)
+      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true, !SCALES>), grid, block, lds, stream,
+                         a, first, slices, units);
+    else if (stream_stores)
+      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true, false>), grid, block, lds, stream, a,
                          first, slices, units);
+    else
+      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, !SCALES, false>), grid, block, lds, stream,
+                         a, first, slices, units);
   });
 }
 
