@@ -418,7 +418,8 @@ hipError_t launch_unit_as(const CombineArgs& a, hipStream_t stream) {
 
 template <int KB>
 hipError_t launch_unit(const CombineArgs& a, hipStream_t stream) {
-  if (KB == 1 && a.row_bytes > 2 * kWaveBytes) return launch_unit_as<KB, KB == 1 ? 4 : 1>(a, stream);
+  if (KB == 1 && a.row_bytes > 2 * kWaveBytes)
+    return launch_unit_as<KB, KB == 1 ? 4 : 1>(a, stream);
   if (KB <= 2 && a.row_bytes > kWaveBytes) return launch_unit_as<KB, KB <= 2 ? 2 : 1>(a, stream);
   return launch_unit_as<KB, 1>(a, stream);
 }

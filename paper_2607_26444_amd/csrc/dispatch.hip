@@ -12,8 +12,8 @@
 // the chip by its slices.
 //
 // Explicit splits (dispatch_kernel; moe_dispatch_ex with a policy, a
-// wavefront count or a trace): persistent wavefronts over the byte-balanced plan (Section 6.2 with one
-// memory tier, Appendix D third level).  moe_layout leaves MOE_PLAN_PARTS
+// wavefront count or a trace): persistent wavefronts over the byte-balanced
+// plan (Section 6.2 with one memory tier, Appendix D third level).  moe_layout leaves MOE_PLAN_PARTS
 // contiguous token ranges of equal byte cost; wavefront g of W takes parts g,
 // g + W, g + 2W, ... or claims parts in plan order at run time.  A wavefront
 // reads its token's whole row into registers and stores it to each of the k

@@ -66,8 +66,8 @@ int copy_waves(const void* kernel, int64_t per_wave, int64_t target, int min_wav
 constexpr int64_t kDispatchInFlight = 64ll << 20;
 constexpr int64_t kCombineInFlight = 16ll << 20;
 
-// The default split (MOE_POLICY_BALANCED) of combine and expand hands every
-// part out at run time when a part carries at least this many algorithmic
+// The persistent combine under MOE_POLICY_BALANCED (a wavefront count or a
+// trace) hands every part out at run time when a part carries at least this many algorithmic
 // bytes on average (tokens * row bytes * (1 + rows per token) /
 // MOE_PLAN_PARTS).  Measured on MI355X with a fresh x per step: claiming
 // every part made combine 2-4% faster at 168-192 KiB per part (prefill,
@@ -75,13 +75,10 @@ constexpr int64_t kCombineInFlight = 16ll << 20;
 // (decode: 104.5 vs 87.8 us), where one claim serves a third of a token.
 constexpr int64_t kClaimAllPartBytes = 128ll << 10;
 
-// Dispatch (per-slot rows and the per-peer path's pair rows) claims every
-// part from half that size.  With sharded tickets, claiming every part
-// measured 1.8% faster for the fp8 workload's 84 KiB parts (215 vs 219 us)
-// and tied at decode size (42 KiB, which keeps the half-claimed split);
-// pair rows measured 4% faster at 93 KiB per part (Zipf-skewed prefill)
-// and 0.6% at 107 KiB, where the same split of the source-side sum was 2-5%
-// slower and stays at the default.
+// The persistent dispatch claims every part from half that size.  With sharded
+// tickets, claiming every part measured 1.8% faster for the fp8 workload's 84
+// KiB parts (215 vs 219 us) and tied at decode size (42 KiB, which keeps the
+// half-claimed split).
 constexpr int64_t kClaimAllDispatchPartBytes = 64ll << 10;
 
 __host__ __forceinline__ bool claim_all_parts(int64_t tokens, int64_t row_bytes, int64_t rows,
@@ -247,14 +244,12 @@ __device__ __forceinline__ u32x4 ld16_stream(const void* p) {
 __device__ __forceinline__ void st16_stream(void* p, u32x4 v) {
   __builtin_nontemporal_store(v, (gu32x4*)(uintptr_t)p);
 }
-// Row stores of the persistent dispatch, VPL KiB per pass: non-temporal for rows of more than 8 KiB, ordinary for narrower rows.
+// Row stores of the persistent dispatch, VPL KiB per pass: non-temporal for
+// rows of more than 8 KiB, ordinary for narrower rows.
 // Measured in whole steps on MI355X: non-temporal stores are 8-12% faster
 // for dispatch's 14 KiB rows (prefill, decode), ordinary stores 4% faster
 // for the fp8 workload's 7 KiB rows (211 vs 220 us) and 2.5% for the 8 KiB
-// rows of the large workload (444 vs 455 us); in the per-peer chain,
-// ordinary stores made expand 6% faster for those rows (fp8 445 -> 418 us,
-// large 668 -> 635) and the pair dispatch after it 8-10% slower, 0.5% less
-// for the chain.
+// rows of the large workload (444 vs 455 us).
 template <int VPL>
 __device__ __forceinline__ void store_row16(void* p, u32x4 v) {
   if constexpr (VPL > 8)
