@@ -125,6 +125,20 @@ def test_fixed_capacity_forms_match_oracle(T, E, R, k, C):
     _check(lay, idx, E, R, capacity=C, what=f"fixed T={T} C={C}")
 
 
+@pytest.mark.parametrize("T,E,k", [(0, 5, 2), (1, 256, 8), (64, 256, 8), (300, 7, 3), (700, 1024, 4),
+                                   (2600, 1, 1)])
+@pytest.mark.parametrize("C", [1, 3, 63, 64, 65, 200, 1027])
+def test_fixed_capacity_unfilled_window_rows(T, E, k, C):
+    """Every window row no slot fills gets -1, for windows narrower and wider
+    than a wavefront, and fewer and more of them than wavefronts."""
+    from paper_2607_26444_amd import moe
+    idx = _routing(T, k, E, seed=T + C, mask=0.2)
+    lay = moe.Layout(T, k, E, 1, capacity=C)
+    lay.row_src.fill_(0x5A5A)
+    lay.run(torch.from_numpy(idx).cuda())
+    _check(lay, idx, E, 1, capacity=C, what=f"windows T={T} E={E} C={C}")
+
+
 @pytest.mark.parametrize("T", [8192, 32768])
 @pytest.mark.parametrize("fill", ["zeros", "ones", "arange", "other_batch"])
 def test_fused_barrier_with_leftover_workspace(fill, T):
