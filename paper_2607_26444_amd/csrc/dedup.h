@@ -31,7 +31,6 @@ struct ExpandArgs {
   int64_t row_bytes;
   int32_t scale_row_bytes;
   int32_t scale_pitch;
-  int32_t off_line;              // slices cut at the destination's lines (set by the launch)
   int32_t scales16;              // scale rows move in 16-byte pieces, at most 1 KiB of them
   int32_t k;
   int32_t L;

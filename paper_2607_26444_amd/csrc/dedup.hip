@@ -107,28 +107,37 @@ __global__ __launch_bounds__(kBlock) void expand_unit_kernel(ExpandArgs a, int f
     }
     if (!src || !dst) src = dst = 0;
   }
-  // row offset of the slice's first byte in slot j's destination (rows_off_line)
-  const uint32_t line = a.off_line ? kLine - 1 : 0;
+  // a slice of each destination row is cut at that row's own 128-byte lines:
+  // it starts `cut` bytes early, and the last slice ends with the row (16384 x
+  // 14 KiB, k = 8, region bases 16 bytes off the line: 752 us for whole rows
+  // per wavefront, 804 with uncut slices, 731 now)
   for (int j0 = 0; j0 < k; j0 += KB) {
     u32x4 v[KB][S];
 #pragma unroll
     for (int j = 0; j < KB; ++j) {
       const uint64_t base = readlane64(src, j0 + j);
-      const uint32_t o = o0 - ((uint32_t)readlane64(dst, j0 + j) & line);
+      const uint32_t cut = (uint32_t)readlane64(dst, j0 + j) % kLine;
       const Rsrc rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<uint8_t*>(base),
                                                         (short)0, base ? (int)rb : 0, kRsrcWord3);
 #pragma unroll
       for (int c = 0; c < S; ++c)
-        v[j][c] = __builtin_amdgcn_raw_buffer_load_b128(rs, o + c * kWaveBytes, 0, 0);
+        v[j][c] = __builtin_amdgcn_raw_buffer_load_b128(rs, o0 - cut + c * kWaveBytes, 0, 0);
     }
 #pragma unroll
     for (int j = 0; j < KB; ++j) {
       uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j0 + j));
-      const uint32_t o = o0 - ((uint32_t)(uintptr_t)d & line);
+      if (!d) continue;
+      const uint32_t cut = (uint32_t)(uintptr_t)d % kLine;
 #pragma unroll
       for (int c = 0; c < S; ++c) {
-        const uint32_t off = o + c * kWaveBytes;
-        if (d && off < rb) st16_stream(d + off, v[j][c]);
+        const uint32_t off = o0 - cut + c * kWaveBytes;   // wraps before the row's start
+        if (off < rb) st16_stream(d + off, v[j][c]);
+      }
+      if (cut && q == slices - 1) {
+        const uint32_t off = o0 + (S - 1) * kWaveBytes;
+        const uint8_t* from = reinterpret_cast<const uint8_t*>(readlane64(src, j0 + j));
+        if (lane * kVecBytes + cut >= kWaveBytes && off < rb)
+          st16_stream(d + off, ld16(from + off));
       }
     }
   }
@@ -289,7 +298,7 @@ __global__ __launch_bounds__(kBlock) void combine_local_unit_kernel(LocalArgs a,
 
 template <bool SCALES, int KB, int S>
 hipError_t launch_expand_as(const ExpandArgs& a, hipStream_t stream) {
-  const int slices = unit_slices(a.row_bytes, S);
+  const int slices = (int)((row_slices(a.row_bytes) + S - 1) / S);
   const int64_t width = a.row_bytes < S * kWaveBytes ? a.row_bytes : S * kWaveBytes;
   const unsigned lds = wave_limit_lds(expand_unit_waves(a.k * width), kWavesPerBlock);
   return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
@@ -340,9 +349,7 @@ DedupGeom dedup_geom(int64_t T, int k, int R) {
   return d;
 }
 
-hipError_t launch_expand(const ExpandArgs& args, hipStream_t stream) {
-  ExpandArgs a = args;
-  a.off_line = rows_off_line(a.row_bytes);
+hipError_t launch_expand(const ExpandArgs& a, hipStream_t stream) {
   return a.dedup_scales ? launch_expand_units<true>(a, stream)
                         : launch_expand_units<false>(a, stream);
 }

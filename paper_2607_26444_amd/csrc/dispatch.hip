@@ -199,6 +199,17 @@ __global__ __launch_bounds__(kBlock) void dispatch_kernel(DispatchArgs a) {
   trace_wave(a.trace, a.trace_waves, g, t_start, lane);
 }
 
+// Lane l's value of lane (l - n) mod 64, n wavefront-uniform.
+__device__ __forceinline__ u32x4 rotate_up(u32x4 v, int n, int lane) {
+  const int from = ((lane - n) & (kWave - 1)) * 4;
+  u32x4 r;
+  r.x = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.x);
+  r.y = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.y);
+  r.z = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.z);
+  r.w = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.w);
+  return r;
+}
+
 template <bool NT>
 __device__ __forceinline__ void store16(void* p, u32x4 v) {
   if constexpr (NT)
@@ -237,12 +248,28 @@ __device__ __forceinline__ void store16(void* p, u32x4 v) {
 // groups of `pieces` lanes, one group per destination, so one store
 // instruction writes 64 / pieces scale rows whole.
 //
-// SHIFT (rows_off_line): the slices of each destination row are cut at its
-// line boundaries, so a destination's bytes are loaded at an offset of its own,
-// KB destinations at a time, from the caches (us, persistent split -> this:
-// 16384 x 14352 B, k = 8, 470 -> 414; 8192 x 8208 B, k = 8, 129 -> 118; 4770 x
-// 6752 B, k = 6, 51 -> 43; 2000 x 12304 B, k = 4, 27 -> 22.6).
-template <bool SCALES, bool NT, bool SHIFT>
+// Destination rows that start inside a 128-byte line (rows that are no
+// multiple of a line, or a region whose base is not on one): the slices of
+// such a row are cut at its lines, so that no line is written in part by two
+// wavefronts except where two rows meet.  Each lane's piece moves up by `cut`
+// lanes through the LDS crossbar and the last pieces of the slice before it
+// (pv, one 7-lane load, from the caches) come in from below; the last slice
+// also stores the row's end.  Rows on the line whose region starts at half a
+// line are left as they are: writing half lines measured as fast.  pv is
+// requested with the slice where the row width says that it is needed, else
+// only once a destination asks for it.  us on MI355X, persistent split (a row
+// per wavefront) / uncut slices / this:
+//   16384 x 14 KiB, k = 8, bases 16 bytes off    431 595 468 (Zipf 407 561 455)
+//   4096 x 14 KiB, k = 8, bases 16 bytes off     115 154 119
+//   16384 x 8 KiB, k = 8, bases 16 / 64 off      243 340 272 / 231 247 246
+//   16384 x 4 KiB, k = 8, bases 16 / 64 off      142 168 136 / 133 117 118
+// and with the rows themselves off the line, persistent split / a load of its
+// own per destination / this:
+//   16384 x 14352 B, k = 8 / 2 / 1    437 414 418 / 151 198 141 / 96 159 95
+//   16384 x 8208 B, k = 9 / 6         312 324 293 / 202 197 198
+//   4770 x 6752 B, k = 6              41 50 48 (39 with the stores of launch_unit)
+//   16384 x 14400 B, k = 8            442 435 424 (an odd multiple of 64 bytes)
+template <bool SCALES, bool NT, int S>
 __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, int first,
                                                                int slices, int units) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -253,14 +280,24 @@ __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, i
   const uint32_t sb = (uint32_t)a.scale_row_bytes;
   const uint32_t sp = (uint32_t)a.scale_pitch;
   const int k = a.k;
-  const uint32_t off = (uint32_t)q * kWaveBytes + lane * kVecBytes;
+  const uint32_t off = (uint32_t)q * (S * kWaveBytes) + lane * kVecBytes;
   int p = -1, e = 0;
   if (lane < k) {
     p = a.pos[(int64_t)t * k + lane];
     e = a.topk_idx[(int64_t)t * k + lane];
   }
-  u32x4 v = {0u, 0u, 0u, 0u}, sv = {0u, 0u, 0u, 0u};
-  if (!SHIFT && off < rb) v = ld16(a.x + (int64_t)t * rb + off);
+  // v: this lane's piece of the slice; pv: the last pieces of the slice
+  // before it, in the same lanes
+  const uint8_t* row = a.x + (int64_t)t * rb;
+  u32x4 v[S], pv = {0u, 0u, 0u, 0u}, sv = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int c = 0; c < S; ++c) {
+    v[c] = u32x4{0u, 0u, 0u, 0u};
+    if (off + c * kWaveBytes < rb) v[c] = ld16(row + off + c * kWaveBytes);
+  }
+  const bool before = q > 0 && lane >= kWave - (int)(kLine / kVecBytes - 1);
+  const bool off_line = rb % kLine != 0;
+  if (off_line && before) pv = ld16(row + off - kWaveBytes);
   const uint8_t* ssrc = SCALES ? a.x_scales + (int64_t)t * sb : nullptr;
   const bool scales_here = SCALES && q == 0;
   const int pieces = (int)sp / kVecBytes;
@@ -292,29 +329,37 @@ __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, i
       }
     }
   }
-  if constexpr (SHIFT) {
-    constexpr int KB = 8;
-    const Rsrc row = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(a.x + (int64_t)t * rb), (short)0, (int)rb, kRsrcWord3);
-    for (int j0 = 0; j0 < k; j0 += KB) {
-      u32x4 w[KB];
+  // Bytes by which each destination row starts past its line, as far as they
+  // matter: half a line does as well as none where rows are whole lines.
+  const uint32_t in_line = off_line ? kLine - 1 : kLine / 2 - 1;
+  if (!__any(((uint32_t)dst & in_line) != 0)) {
+    for (int j = 0; j < k; ++j) {
+      uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j));
 #pragma unroll
-      for (int j = 0; j < KB; ++j) {
-        // before the row's start or past its end: nothing is read, nothing stored
-        const uint32_t o = off - ((uint32_t)readlane64(dst, j0 + j) & (kLine - 1));
-        w[j] = __builtin_amdgcn_raw_buffer_load_b128(row, o, 0, 0);
-      }
-#pragma unroll
-      for (int j = 0; j < KB; ++j) {
-        uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j0 + j));
-        const uint32_t o = off - ((uint32_t)(uintptr_t)d & (kLine - 1));
-        if (d && o < rb) store16<NT>(d + o, w[j]);
+      for (int c = 0; c < S; ++c) {
+        const uint32_t o = off + c * kWaveBytes;
+        if (d && o < rb) store16<NT>(d + o, v[c]);
       }
     }
   } else {
+    if (!off_line && before) pv = ld16(row + off - kWaveBytes);
     for (int j = 0; j < k; ++j) {
       uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j));
-      if (d && off < rb) store16<NT>(d + off, v);
+      if (!d) continue;
+      // every lane's piece moves up by `cut` lanes; the last ones of the KiB
+      // before it come in from below
+      const uint32_t past = (uint32_t)(uintptr_t)d % kLine;
+      const int cut = past & in_line ? (int)(past / kVecBytes) : 0;
+#pragma unroll
+      for (int c = 0; c < S; ++c) {
+        const u32x4 r = rotate_up(lane + cut < kWave ? v[c] : c > 0 ? v[c > 0 ? c - 1 : 0] : pv,
+                                  cut, lane);
+        const uint32_t o = off + c * kWaveBytes - cut * kVecBytes;   // wraps before the row's start
+        if (o < rb) store16<NT>(d + o, r);
+      }
+      const uint32_t o = off + (S - 1) * kWaveBytes;
+      if (q == slices - 1 && lane + cut >= kWave && o < rb)
+        store16<NT>(d + o, v[S - 1]);
     }
   }
   if (scales_here) {
@@ -373,32 +418,27 @@ constexpr int64_t kScaledStreamBytes = 768ll << 20;
 
 template <bool SCALES>
 hipError_t launch_unit(const DispatchArgs& a, hipStream_t stream) {
-  const int slices = unit_slices(a.row_bytes, 1);
+  const int slices = (int)row_slices(a.row_bytes);
   // One wavefront per workgroup frees its slot as soon as it is done.  With
   // scale rows the slice-0 wavefront lives longer, and workgroups of four
   // measured better at the same limit (fp8, 16384 x 7 KiB: uniform 219 -> 208
   // us, Zipf 202 -> 186).
-  const bool shift = !SCALES && rows_off_line(a.row_bytes);   // fp8 rows are whole lines
-  const int wpb = SCALES || shift ? kWavesPerBlock : 1;
+  const int wpb = SCALES ? kWavesPerBlock : 1;
   const int64_t rows = a.rows_hint > 0 ? a.rows_hint : a.k;
   const bool small_x = !SCALES && a.tokens * a.row_bytes <= (96ll << 20);
   const bool stream_stores = !SCALES || a.tokens * rows * a.row_bytes <= kScaledStreamBytes;
-  // Shifted slices load once per destination and want every wavefront (us at
-  // 32 / 20 / 12: 16384 x 14352 B, k = 8, 414 428 505; 16384 x 8240 B, k = 4,
-  // 155 173 201; 4770 x 6752 B, k = 6, 43 42 39).
-  const unsigned lds =
-      shift ? 0u : wave_limit_lds(dispatch_unit_waves(rows, small_x), wpb);
+  // Rows off the line live longer and want every wavefront.
+  const unsigned lds = a.row_bytes % kLine != 0
+                           ? 0u
+                           : wave_limit_lds(dispatch_unit_waves(rows, small_x), wpb);
   return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
     const dim3 grid((units + wpb - 1) / wpb), block(wpb * kWave);
-    if (shift)
-      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true, !SCALES>), grid, block, lds, stream,
-                         a, first, slices, units);
-    else if (stream_stores)
-      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true, false>), grid, block, lds, stream, a,
+    if (stream_stores)
+      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true, 1>), grid, block, lds, stream, a,
                          first, slices, units);
     else
-      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, !SCALES, false>), grid, block, lds, stream,
-                         a, first, slices, units);
+      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, !SCALES, 1>), grid, block, lds, stream, a,
+                         first, slices, units);
   });
 }
 

@@ -91,19 +91,7 @@ __host__ __forceinline__ bool claim_all_parts(int64_t tokens, int64_t row_bytes,
 __host__ __forceinline__ int64_t row_slices(int64_t row_bytes) {
   return (row_bytes + kWaveBytes - 1) / kWaveBytes;
 }
-// Rows that are no multiple of 64 bytes start anywhere in a 128-byte line.
-// Slices of such a destination row are cut at its line boundaries (the first
-// and last ones are shorter, and a row may take one slice more), so that no
-// line is written in part by two wavefronts except where two rows meet.
-// Non-temporal stores of parts of lines made dispatch 14352-byte rows at 571
-// us and 8208-byte rows at 162 us where the persistent split, one wavefront
-// per row, took 470 and 129 (16384 and 8192 tokens, k = 8).
-constexpr uint32_t kLine = 128;
-__host__ __forceinline__ bool rows_off_line(int64_t row_bytes) { return row_bytes % 64 != 0; }
-__host__ __forceinline__ int unit_slices(int64_t row_bytes, int slice_kib) {
-  const int64_t span = row_bytes + (rows_off_line(row_bytes) ? kLine - kVecBytes : 0);
-  return (int)((row_slices(span) + slice_kib - 1) / slice_kib);
-}
+constexpr uint32_t kLine = 128;   // bytes that HBM and the caches write whole
 
 // Units one launch takes (a grid holds fewer than 2^32 work items in x);
 // larger batches are launched in several token ranges.

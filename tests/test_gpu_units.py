@@ -68,6 +68,56 @@ def test_units_match_oracle_and_persistent_split(T, H, E, R, k, payload, mask, s
     assert run.layout["status"] == again.layout["status"]
 
 
+# row widths of whole lines (fitting the last slice exactly, or not), of odd
+# multiples of 64 bytes and off the line; region bases by bytes past a line,
+# one after another over the regions
+OFF_BASES = [(0,), (16,), (64,), (112, 0, 48)]
+OFF_CASES = [
+    (65, 64, 8, 4, 1, wl.BF16),        # one line
+    (65, 512, 16, 4, 2, wl.BF16),      # 1 KiB: the whole last slice
+    (65, 520, 16, 4, 2, wl.BF16),      # 1 KiB + 16 B
+    (65, 568, 16, 4, 3, wl.BF16),      # 1 KiB + 112 B
+    (65, 544, 16, 8, 8, wl.BF16),      # 1 KiB + 64 B
+    (65, 1016, 16, 4, 1, wl.BF16),     # 2 KiB - 16 B
+    (65, 1024, 16, 4, 1, wl.BF16),
+    (40, 2048, 64, 16, 9, wl.BF16),    # 4 KiB
+    (40, 2056, 64, 16, 17, wl.BF16),
+    (30, 7168, 64, 16, 8, wl.BF16),
+    (30, 7176, 64, 16, 4, wl.BF16),
+    (65, 128, 16, 4, 2, wl.FP8_E4M3),
+    (65, 1024, 16, 4, 3, wl.FP8_E4M3),
+    (30, 7168, 64, 16, 8, wl.FP8_E4M3),
+]
+
+
+@pytest.fixture(params=OFF_BASES, ids=str)
+def off_bases(request, monkeypatch):
+    """Regions whose bases lie the given bytes past a 4 KiB boundary."""
+    from paper_2607_26444_amd import moe
+
+    class Shifted(moe.Regions):
+        def __init__(self, rows, row_bytes, **kw):
+            super().__init__(rows, row_bytes, **kw)   # guards are wider than the shift
+            by = [request.param[r % len(request.param)] for r in range(len(self.rows))]
+            self.offsets = [o + b for o, b in zip(self.offsets, by)]
+            self.table += torch.tensor(by, device=self.table.device)
+
+    monkeypatch.setattr(moe, "Regions", Shifted)
+
+
+@pytest.mark.parametrize("T,H,E,R,k,payload", OFF_CASES)
+def test_rows_that_start_inside_a_line(T, H, E, R, k, payload, off_bases):
+    """Dispatch, and the per-peer chain, into destination rows that start
+    anywhere in a 128-byte line, every byte of the regions and around them."""
+    from test_gpu_dedup import _dedup_parity
+    from test_gpu_parity import _full_parity
+    cfg = wl.custom(T, H, E, R, k, payload=payload, zipf_s=1.2, seed=T + H + k)
+    inp = wl.make_inputs(cfg)
+    idx = wl.mask_slots(inp["topk_idx"], 0.1, seed=k)
+    _full_parity(cfg, inp, idx=idx, spare_rows=1)
+    _dedup_parity(cfg, inp, idx=idx)
+
+
 def test_more_units_than_one_launch():
     """2^24 + 5 one-slice tokens: the units go out in two launches.  k = 1 and
     unit weights, so y is x bit for bit and every region row is its token's."""
