@@ -223,25 +223,29 @@ __device__ __forceinline__ void store16(void* p, u32x4 v) {
 // Bound by HBM writes (one read per k writes).  What sets the rate is how
 // many row stores are in flight over the chip: too few leave HBM idle, too
 // many open more destination rows than its pages serve well, so the launch
-// limits the resident wavefronts (dispatch_unit_waves).  A slice of 1 KiB
-// (one 16-byte store per lane and destination) holds the fewest bytes per
-// wavefront; 2 and 4 KiB slices measured 0-3% slower at their best limit.
+// limits the resident wavefronts (launch_unit).  S: slices of S KiB, one
+// 16-byte store per lane, KiB and destination; 1 KiB holds the fewest bytes per
+// wavefront.
 // Metadata is the token's k slots, one lane each, read by every slice (one
 // line, from the caches); the destinations are read back by lane, so neither
 // LDS nor a barrier is needed.  Measured on MI355X against the persistent
 // split below (us before -> after, GB/s of algorithmic bytes after):
-//   16384 x 14 KiB, k = 8, Zipf 1.2 routing   384 -> 358  (5900)
-//   32768 x 8 KiB, k = 8, Zipf 1.5            444 -> 410  (5890)
-//   8192 x 14 KiB, k = 16, uniform            524 -> 400  (5000)
-//   32768 x 512 B, k = 8                      41.3 -> 26  (5800)
-//   512 x 14 KiB, k = 8                       22.6 -> 12.4
-//   4096 x 14 KiB, k = 8, uniform, x cached   91.5 -> 92   (5750)
-//   8192 x 7 KiB fp8, k = 8, uniform / Zipf   109 / 104 -> 100 / 89
-//   16384 x 8 KiB, k = 8, uniform             221 -> 229  (5270): 256 windows
-//   of wide rows written at once are the one range where it is slower
-// NT: non-temporal stores; ordinary ones were 0-30% slower (8 KiB rows Zipf
-// 413 -> 434, 2 KiB rows 53 -> 67, 14 KiB rows at 4096 tokens 94 -> 102)
-// except for very large fp8 batches (kScaledStreamBytes).
+//   16384 x 14 KiB, k = 8, Zipf 1.2 routing   380 -> 361  (5860)
+//   16384 x 14 KiB, k = 8, uniform            401 -> 399  (5300)
+//   32768 x 8 KiB, k = 8, Zipf 1.5            445 -> 416  (5800)
+//   16384 x 8 KiB, k = 8, uniform             221 -> 218  (5540)
+//   8192 x 14 KiB, k = 16, uniform            508 -> 398  (5020)
+//   4096 x 14 KiB, k = 8, uniform, x in HBM / cached   104 -> 101 / 92 -> 93
+//   16384 x 2 KiB, k = 8, uniform             58 -> 50  (6040)
+//   32768 x 512 B, k = 8                      36.5 -> 27.9  (5410)
+//   512 x 14 KiB, k = 8                       22.6 -> 12.7
+//   16384 x 7 KiB fp8, k = 8, Zipf            197 -> 190
+// Slower: batches with most slots unused, whose wavefronts are bound by their
+// metadata chain and, at 32768 x 14 KiB, by the launch of so many of them
+// (half of the slots unused 457 -> 503, nine tenths 190 -> 287; at 4096 tokens
+// 34 -> 38), and batches whose x the Infinity Cache holds whole (16384 x 14
+// KiB, k = 8: 343 -> 359).
+// NT: non-temporal stores.  CUT_NT: the same for rows that start inside a line.
 //
 // SCALES: the wavefront of slice 0 also carries the token's scale row: sized
 // in 16-byte multiples and at most 1 KiB, its pitched bytes are spread over
@@ -259,17 +263,17 @@ __device__ __forceinline__ void store16(void* p, u32x4 v) {
 // requested with the slice where the row width says that it is needed, else
 // only once a destination asks for it.  us on MI355X, persistent split (a row
 // per wavefront) / uncut slices / this:
-//   16384 x 14 KiB, k = 8, bases 16 bytes off    431 595 468 (Zipf 407 561 455)
-//   4096 x 14 KiB, k = 8, bases 16 bytes off     115 154 119
-//   16384 x 8 KiB, k = 8, bases 16 / 64 off      243 340 272 / 231 247 246
-//   16384 x 4 KiB, k = 8, bases 16 / 64 off      142 168 136 / 133 117 118
+//   16384 x 14 KiB, k = 8, bases 16 / 64 bytes off  431 602 413 / 406 436 422
+//   4096 x 14 KiB, k = 8, bases 16 bytes off        115 154 108
+//   16384 x 8 KiB, k = 8, bases 16 / 64 off         243 345 259 / 231 249 237
+//   16384 x 4 KiB, k = 8, bases 16 / 64 off         142 168 135 / 134 118 117
 // and with the rows themselves off the line, persistent split / a load of its
 // own per destination / this:
 //   16384 x 14352 B, k = 8 / 2 / 1    437 414 418 / 151 198 141 / 96 159 95
 //   16384 x 8208 B, k = 9 / 6         312 324 293 / 202 197 198
-//   4770 x 6752 B, k = 6              41 50 48 (39 with the stores of launch_unit)
+//   4770 x 6752 B, k = 6              41 50 39
 //   16384 x 14400 B, k = 8            442 435 424 (an odd multiple of 64 bytes)
-template <bool SCALES, bool NT, int S>
+template <bool SCALES, bool NT, bool CUT_NT, int S>
 __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, int first,
                                                                int slices, int units) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -332,35 +336,34 @@ __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, i
   // Bytes by which each destination row starts past its line, as far as they
   // matter: half a line does as well as none where rows are whole lines.
   const uint32_t in_line = off_line ? kLine - 1 : kLine / 2 - 1;
-  if (!__any(((uint32_t)dst & in_line) != 0)) {
-    for (int j = 0; j < k; ++j) {
-      uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j));
+  if (!off_line && __any(((uint32_t)dst & in_line) != 0) && before)
+    pv = ld16(row + off - kWaveBytes);
+  for (int j = 0; j < k; ++j) {
+    uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j));
+    if (!d) continue;
+    const uint32_t past = (uint32_t)(uintptr_t)d % kLine;
+    const int cut = past & in_line ? (int)(past / kVecBytes) : 0;
+    if (cut == 0) {
 #pragma unroll
       for (int c = 0; c < S; ++c) {
         const uint32_t o = off + c * kWaveBytes;
-        if (d && o < rb) store16<NT>(d + o, v[c]);
+        if (o < rb) store16<NT>(d + o, v[c]);
       }
+      continue;
     }
-  } else {
-    if (!off_line && before) pv = ld16(row + off - kWaveBytes);
-    for (int j = 0; j < k; ++j) {
-      uint8_t* d = reinterpret_cast<uint8_t*>(readlane64(dst, j));
-      if (!d) continue;
-      // every lane's piece moves up by `cut` lanes; the last ones of the KiB
-      // before it come in from below
-      const uint32_t past = (uint32_t)(uintptr_t)d % kLine;
-      const int cut = past & in_line ? (int)(past / kVecBytes) : 0;
+    // every lane's piece moves up by `cut` lanes; the last ones of the KiB
+    // before it come in from below
 #pragma unroll
-      for (int c = 0; c < S; ++c) {
-        const u32x4 r = rotate_up(lane + cut < kWave ? v[c] : c > 0 ? v[c > 0 ? c - 1 : 0] : pv,
-                                  cut, lane);
-        const uint32_t o = off + c * kWaveBytes - cut * kVecBytes;   // wraps before the row's start
-        if (o < rb) store16<NT>(d + o, r);
-      }
-      const uint32_t o = off + (S - 1) * kWaveBytes;
-      if (q == slices - 1 && lane + cut >= kWave && o < rb)
-        store16<NT>(d + o, v[S - 1]);
+    for (int c = 0; c < S; ++c) {
+      const u32x4 r = rotate_up(lane + cut < kWave ? v[c] : c > 0 ? v[c > 0 ? c - 1 : 0] : pv, cut,
+                                lane);
+      const uint32_t o = off + c * kWaveBytes - cut * kVecBytes;   // wraps before the row's start
+      if (o < rb) store16<CUT_NT>(d + o, r);
     }
+    const uint32_t o = off + (S - 1) * kWaveBytes;
+    if (q == slices - 1 && lane + cut >= kWave && o < rb) store16<CUT_NT>(d + o, v[S - 1]);
+    // the two kinds of store are not joined, which would drop the hint of both
+    if constexpr (NT != CUT_NT) __builtin_amdgcn_wave_barrier();
   }
   if (scales_here) {
     if (s16) {
@@ -390,56 +393,87 @@ __global__ __launch_bounds__(kBlock) void dispatch_unit_kernel(DispatchArgs a, i
   }
 }
 
-// Resident wavefronts per compute unit for `rows` stores of 1 KiB per
-// wavefront: about 96 KiB of stores in flight for 8 (12 wavefronts), more
-// wavefronts for fewer, whose lives are mostly load latency.  Pair rows are
-// sized for about half the slots: under Zipf routing 12 wavefronts made the
-// per-peer chain 3% slower than 18 (1594 -> 1545 us at 16384 x 14 KiB), under
-// uniform routing 0.7% faster (593 -> 597 at 4096 tokens).  Measured
-// on MI355X (16384 x 14 KiB; us at 32 / 18 / 14 / 12 / 9 wavefronts):
-//   k = 8, Zipf  388 377 360 358 392     k = 8, uniform  421 413 408 397 -
-//   k = 6 (10 KiB rows)  229 219 215 224 -      k = 4  228 216 230 247 -
-//   k = 2  134 145 167 183 -     k = 16 (8192 tokens)  404 385 399 400 400
-// bf16 batches of at most 96 MiB of x, whose loads the Infinity Cache mostly
-// serves and whose lives are shorter, take two fewer from 8 rows on (whole
-// steps of 4096 x 14 KiB, k = 8, us at 12 / 10 / 8 wavefronts: 192.1 191.2
-// 191.4 with x cached, 203.2 201.7 209.4 with x in HBM).
-int dispatch_unit_waves(int64_t rows, bool small_x) {
-  if (rows < 8) return (int)(48 / rows) + 6;
-  return small_x ? 10 : 12;
+template <bool SCALES, bool NT, int S, bool CUT_NT = NT>
+hipError_t launch_unit_as(const DispatchArgs& a, int waves, int wpb, hipStream_t stream) {
+  const int slices = (int)((row_slices(a.row_bytes) + S - 1) / S);
+  const unsigned lds = wave_limit_lds(waves, wpb);
+  return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
+    hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, NT, CUT_NT, S>),
+                       dim3((units + wpb - 1) / wpb), dim3(wpb * kWave), lds, stream, a, first,
+                       slices, units);
+  });
 }
 
-// Rows with scale rows are stored non-temporally up to this many row bytes in
-// all and with ordinary stores beyond (fp8 7 KiB rows, k = 8, us
-// non-temporal / ordinary: 4096 tokens 49 / 54, 8192 100 / 107, 12288 148 /
-// 152; at 16384, 896 MiB, uniform routing 211 / 205 and Zipf 187 / 194, where
-// the persistent split took 210 and 199).
-constexpr int64_t kScaledStreamBytes = 768ll << 20;
+// Bytes of x and of the rows written that the 256 MiB Infinity Cache takes in:
+// up to here ordinary stores end in it, and beyond non-temporal ones are the
+// better choice; from kAbsorbedMin on they gain (below, a launch is too short).
+constexpr int64_t kAbsorbedMin = 96ll << 20, kAbsorbedMax = 300ll << 20;
 
+// How the units are launched.  What bounds a batch is, by size: launch latency
+// and the metadata chain (small ones), the Infinity Cache (up to
+// kAbsorbedMax), HBM writes (beyond).  All figures us on MI355X with x from
+// HBM / re-read from the caches, "persistent" the split of launch_scales.
+//
+// 1. Rows under 1 KiB (a partly filled wavefront each): every wavefront
+//    resident, workgroups of four.  32768 x 512 B, k = 8: persistent 37 / 27,
+//    12 resident wavefronts 32 / 28, this 28 / 27; 65536 x 256 B, k = 8: 49 56
+//    32.  Rows off the line take ordinary stores (rows that share a line meet
+//    in L2: 32768 x 528 B, k = 8: persistent 43, non-temporal 49, this 36), and so
+//    does every destination that starts inside a line.
+// 2. Batches that the Infinity Cache absorbs: ordinary stores, slices of 2
+//    KiB, workgroups of four, 24 wavefronts (32 for fewer than 4 rows a
+//    token and for rows off the line, whose lives are longer).  Against the
+//    persistent split and non-temporal 1 KiB units:
+//      16384 x 2 KiB, k = 8    57 / 64   58 / 54   50 / 51
+//      4096 x 4 KiB, k = 8     26 / 25   28 / 27   26 / 24
+//      4096 x 8 KiB, k = 8     50 / 51   57 / 52   49 / 50
+//      32768 x 2 KiB, k = 2    36 / 33   42 / 33   35 / 32
+//      16384 x 8 KiB, k = 1    46 / 45   54 / 47   44 / 41
+//      8192 x 2 KiB fp8, k = 8 27 / 26   33 / 32   27 / 26
+//      4096 x 7 KiB fp8, k = 8 45 / 46   52 / 50   45 / 47
+//      4096 x 6752 B, k = 6    32 / 30   43 / 36   33 / 31
+// 3. Beyond: non-temporal 1 KiB units (2 KiB for one row a token, whose
+//    wavefronts hold least: 16384 x 14 KiB, k = 1: 91 / 81 -> 90 / 70).  About
+//    112 KiB of stores in flight per compute unit for 8 rows a token (14
+//    wavefronts), more wavefronts for fewer, in workgroups of two; fp8 rows,
+//    whose slice-0 wavefront lives longer, in workgroups of four (12
+//    wavefronts; 16384 x 4 KiB, k = 8: of one 131, of two 130, of four 118).
+//    k = 8, persistent / workgroups of one, 12 wavefronts /
+//    of two, 12 / of two, 14 / of two, 16:
+//      16384 x 14 KiB, uniform   399 408 390 398 407      Zipf  377 365 374 359 375
+//      16384 x 10 KiB, uniform   285 289 277 276 286
+//      16384 x 4 KiB, uniform    121 113 113 110 113      Zipf  121 107 110 107 110
+//      4096 x 14 KiB, uniform    104 105 100 101 104      Zipf  98 95 97 94 95
+//      with x re-read from the caches, 16384 x 14 KiB  344 364 359 358 358
+//    k = 4, 14 KiB: persistent 231, 18 wavefronts 221, 14 237; k = 2: 145,
+//    32 130, 14 163; k = 16 (8192 tokens): 506, 14 394.
+//    fp8, k = 8, persistent / ordinary stores / this: 16384 x 7 KiB 207 203 207
+//    (x cached 208 204 192, Zipf 197 194 190), 32768 x 7 KiB 421 405 415.
+//    Rows off the line want every wavefront (16384 x 8240 B, k = 4, at 32 /
+//    20 / 12: 155 173 201), in workgroups of one (16384 x 8256 B, k = 8: 239, of
+//    two 249).
+// 4. ... but rows of 4 to 8 KiB with 8 or more destinations take ordinary
+//    stores: 16384 x 8 KiB over 256 uniform windows, persistent 221 / 222,
+//    non-temporal 225 / 204, this 217 / 219; Zipf 216, 208, 212; 32768
+//    tokens 451, 459, 440, and whole steps 904, 874, 850.
 template <bool SCALES>
 hipError_t launch_unit(const DispatchArgs& a, hipStream_t stream) {
-  const int slices = (int)row_slices(a.row_bytes);
-  // One wavefront per workgroup frees its slot as soon as it is done.  With
-  // scale rows the slice-0 wavefront lives longer, and workgroups of four
-  // measured better at the same limit (fp8, 16384 x 7 KiB: uniform 219 -> 208
-  // us, Zipf 202 -> 186).
-  const int wpb = SCALES ? kWavesPerBlock : 1;
-  const int64_t rows = a.rows_hint > 0 ? a.rows_hint : a.k;
-  const bool small_x = !SCALES && a.tokens * a.row_bytes <= (96ll << 20);
-  const bool stream_stores = !SCALES || a.tokens * rows * a.row_bytes <= kScaledStreamBytes;
-  // Rows off the line live longer and want every wavefront.
-  const unsigned lds = a.row_bytes % kLine != 0
-                           ? 0u
-                           : wave_limit_lds(dispatch_unit_waves(rows, small_x), wpb);
-  return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
-    const dim3 grid((units + wpb - 1) / wpb), block(wpb * kWave);
-    if (stream_stores)
-      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, true, 1>), grid, block, lds, stream, a,
-                         first, slices, units);
-    else
-      hipLaunchKernelGGL((dispatch_unit_kernel<SCALES, !SCALES, 1>), grid, block, lds, stream, a,
-                         first, slices, units);
-  });
+  const int64_t rows = a.rows_hint > 0 ? a.rows_hint : a.k;   // pair rows: half the slots
+  const int64_t touched = a.tokens * a.row_bytes * (rows + 1);
+  const bool off_line = a.row_bytes % kLine != 0;
+  if (a.row_bytes < kWaveBytes)
+    return off_line ? launch_unit_as<SCALES, false, 1>(a, 32, kWavesPerBlock, stream)
+                    : launch_unit_as<SCALES, true, 1, false>(a, 32, kWavesPerBlock, stream);
+  if (touched <= kAbsorbedMax && (touched >= kAbsorbedMin || off_line))
+    return launch_unit_as<SCALES, false, 2>(a, rows < 4 || off_line ? 32 : 24, kWavesPerBlock,
+                                            stream);
+  const int wpb = SCALES ? kWavesPerBlock : off_line ? 1 : 2;
+  if (rows == 1) return launch_unit_as<SCALES, true, 2>(a, 32, wpb, stream);
+  const int waves = off_line ? 32 : rows < 8 ? (int)(48 / rows) + 6 : 14;
+  if (!SCALES && rows >= 8 && !off_line && touched > kAbsorbedMax &&
+      a.row_bytes > 4 * kWaveBytes && a.row_bytes <= 8 * kWaveBytes)
+    return launch_unit_as<SCALES, false, 1>(a, waves, wpb, stream);
+  return launch_unit_as<SCALES, true, 1>(a, waves, wpb, stream);
 }
 
 // Pull dispatch for the partitioning study: a wavefront walks a range of
@@ -636,9 +670,16 @@ hipError_t launch_scales(const DispatchArgs& a, int policy, hipStream_t stream) 
 
 }  // namespace
 
+// Rows of less than a line fill so little of a wavefront that the launch of one
+// per token bounds the units: they keep the persistent split, static parts
+// (262144 x 16 B, k = 1: units 66 us, persistent 40; 32768 x 16 B, k = 8: 18,
+// 16.5; 131072 x 128 B, k = 8: 58, 72).
 hipError_t launch_dispatch(const DispatchArgs& a, int policy, hipStream_t stream) {
-  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace)
-    return a.x_scales ? launch_unit<true>(a, stream) : launch_unit<false>(a, stream);
+  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace) {
+    if (a.row_bytes >= kLine)
+      return a.x_scales ? launch_unit<true>(a, stream) : launch_unit<false>(a, stream);
+    policy = MOE_POLICY_STATIC;
+  }
   return a.x_scales ? launch_scales<true>(a, policy, stream)
                     : launch_scales<false>(a, policy, stream);
 }

@@ -42,6 +42,14 @@ CASES = [
     (130, 1152, 32, 8, 3, wl.FP8_E4M3, 0.2, True),      # 36-byte scale rows, pitch 128
     (130, 7168, 64, 16, 8, wl.FP8_E4M3, 0.1, True),     # 224-byte scale rows, pitch 256
     (40, 33280, 16, 4, 4, wl.FP8_E4M3, 0.1, False),     # scale rows of more than 1 KiB
+    (65, 56, 16, 4, 3, wl.BF16, 0.1, True),             # rows of less than a line: not units
+    (63, 1024, 16, 8, 1, wl.BF16, 0.1, False),          # k = 1: slices of 2 KiB
+    (63, 1536, 16, 8, 1, wl.BF16, 0.1, True),           # ... and a last one of 1 KiB
+    # 96 to 300 MiB of x and rows: ordinary stores, slices of 2 KiB
+    (4100, 2048, 64, 16, 8, wl.BF16, 0.0, True),
+    (16000, 1536, 64, 16, 3, wl.BF16, 0.1, False),
+    (6000, 1544, 64, 16, 8, wl.BF16, 0.1, True),        # off the line
+    (7000, 2048, 64, 16, 8, wl.FP8_E4M3, 0.1, True),
 ]
 
 
