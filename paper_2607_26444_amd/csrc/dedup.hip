@@ -47,18 +47,18 @@ __device__ __forceinline__ int run_row(int key, int tok_pos, int k) {
 // cheaper than walking the runs of a peer one load after another.  Measured on
 // MI355X against persistent wavefronts that did that over whole rows (us
 // before -> after, GB/s of algorithmic bytes after):
-//   16384 x 14 KiB, k = 8, Zipf 1.2     546 -> 499  (5740)
-//   32768 x 8 KiB, k = 8, Zipf 1.5      624 -> 548  (5760)
-//   16384 x 10 KiB, k = 6, uniform      374 -> 342  (5610)
-//   16384 x 7 KiB fp8, k = 8, uniform   396 -> 386  (4950)
-//   4096 x 14 KiB, k = 8, uniform       192 -> 190  (4860)
-//   8192 x 8 KiB, k = 16, uniform       408 -> 414: the one slower range
+//   16384 x 14 KiB, k = 8, Zipf 1.2     546 -> 502  (5710)
+//   32768 x 8 KiB, k = 8, Zipf 1.5      624 -> 551  (5730)
+//   16384 x 10 KiB, k = 6, uniform      401 -> 388
+//   16384 x 7 KiB fp8, k = 8, uniform   397 -> 394
+//   4096 x 14 KiB, k = 8, uniform       190 -> 185  (4990)
+//   8192 x 8 KiB, k = 16, uniform       406 -> 411
 //   16384 x 2 KiB, k = 1                16.9 -> 14.1
 template <bool SCALES, int KB, int S>
 __global__ __launch_bounds__(kBlock) void expand_unit_kernel(ExpandArgs a, int first, int slices,
                                                              int units) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int u = uniform(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave);
+  const int u = uniform(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
   if (u >= units) return;
   const int q = u % slices, t = first + u / slices;
   const uint32_t rb = (uint32_t)a.row_bytes;
@@ -176,16 +176,15 @@ __global__ __launch_bounds__(kBlock) void expand_unit_kernel(ExpandArgs a, int f
 }
 
 // Resident wavefronts per compute unit of the expansion for wave_bytes of
-// loads and as many of stores per wavefront.  Measured on MI355X (us at 32 /
-// 20 / 16 / 12 / 8 wavefronts): 16384 x 14 KiB k = 8 Zipf 517 505 520 499 518,
-// 32768 x 8 KiB k = 8 Zipf 572 547 553 548 578, 16384 x 10 KiB k = 6 353 354
-// 354 342 351, 16384 x 14 KiB k = 4 375 372 369 378 410 and k = 1 98 98 98 100
-// 115, 8192 x 8 KiB k = 10 266 267 266 266 263 and k = 16 413 417 421 420 414,
-// 16384 x 2 KiB k = 1 13.4 14.9 15.7 17.9 20.7.
+// loads and as many of stores per wavefront.  The range of unmasked batches is
+// flat from 12 to 20 wavefronts (16384 x 14 KiB, k = 8, Zipf, us at 32 / 20 /
+// 16 / 12 / 8: 517 505 502 499 518; uniform 736 736 736 735 721); batches with
+// unused slots, whose wavefronts move little each, want more (32768 x 14 KiB,
+// k = 8, half / three quarters / nine tenths unused: 12 wavefronts 770 585 417,
+// 16 750 527 347, one persistent wavefront per row 745 384 157).
 int expand_unit_waves(int64_t wave_bytes) {
-  if (wave_bytes > 8 * kWaveBytes) return 8;
   const int64_t w = 48 * kWaveBytes / wave_bytes + 6;
-  return w < 12 ? 12 : w > 32 ? 32 : (int)w;
+  return w < 16 ? 16 : w > 32 ? 32 : (int)w;
 }
 
 // One wavefront per (token, slice of S KiB of its row): the partial combine.
@@ -296,15 +295,18 @@ __global__ __launch_bounds__(kBlock) void combine_local_unit_kernel(LocalArgs a,
   }
 }
 
+// Workgroups of one wavefront, which frees its slot as soon as it is done, of
+// two with scale rows (16384 x 14 KiB, k = 8, Zipf, us by one / two / four:
+// 502 504 507; 16384 x 8 KiB 412 416 420; fp8 16384 x 7 KiB 396 394 397).
 template <bool SCALES, int KB, int S>
 hipError_t launch_expand_as(const ExpandArgs& a, hipStream_t stream) {
   const int slices = (int)((row_slices(a.row_bytes) + S - 1) / S);
   const int64_t width = a.row_bytes < S * kWaveBytes ? a.row_bytes : S * kWaveBytes;
-  const unsigned lds = wave_limit_lds(expand_unit_waves(a.k * width), kWavesPerBlock);
+  const int wpb = SCALES ? 2 : 1;
+  const unsigned lds = wave_limit_lds(expand_unit_waves(a.k * width), wpb);
   return launch_token_ranges(a.tokens, slices, [&](int first, int units) {
-    hipLaunchKernelGGL((expand_unit_kernel<SCALES, KB, S>),
-                       dim3((units + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), lds,
-                       stream, a, first, slices, units);
+    hipLaunchKernelGGL((expand_unit_kernel<SCALES, KB, S>), dim3((units + wpb - 1) / wpb),
+                       dim3(wpb * kWave), lds, stream, a, first, slices, units);
   });
 }
 
