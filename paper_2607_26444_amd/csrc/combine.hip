@@ -437,11 +437,28 @@ hipError_t launch_units(const CombineArgs& a, hipStream_t stream) {
   }
 }
 
+// Large batches of few, narrow rows per token: a unit is then a fraction of a
+// wavefront's lanes and a chain of three loads, and the launch of one per token
+// bounds the batch.  They keep the persistent split, static parts, whose
+// wavefronts resolve 64 / k tokens at once.  us, persistent / units at 32768,
+// 65536 and 131072 tokens:
+//   k = 1, 16 B    11.8 / 11.0  22.6 / 24.5  39.5 / 47.0     512 B  17.3 / 16.9  30.6 / 31.4  55.7 / 60.7
+//   k = 2, 128 B   14.6 / 17.5  23.1 / 32.6  45.0 / 62.8    1 KiB   22.4 / 24.2  39.1 / 44.8  73.6 / 87.1
+//   k = 3, 512 B   22.9 / 21.9  38.9 / 41.0  69.5 / 79.2    1 KiB   27.5 / 26.5  51.4 / 50.7  -
+//   k = 4, 128 B   18.5 / 19.9  31.4 / 36.7  55.1 / 70.5    1 KiB   31.4 / 30.3  60.7 / 56.7  -
+//   k = 6, 512 B   44.0 / 24.5  76.6 / 46.0  - (its slots are padded to 8)
+bool many_narrow_rows(const CombineArgs& a) {
+  if (a.k > 4 || a.row_bytes > (a.k <= 2 ? 1024 : 512)) return false;
+  return a.tokens >= (a.k % 2 == 0 ? 32768 : 65536);
+}
+
 }  // namespace
 
 hipError_t launch_combine(const CombineArgs& a, int policy, hipStream_t stream) {
-  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace)
-    return launch_units(a, stream);
+  if (policy == MOE_POLICY_BALANCED && a.launch_waves == 0 && !a.trace) {
+    if (!many_narrow_rows(a)) return launch_units(a, stream);
+    policy = MOE_POLICY_STATIC;
+  }
   const bool large = claim_all_parts(a.tokens, a.row_bytes, a.k);
   const bool claim = policy == MOE_POLICY_DYNAMIC || (policy == MOE_POLICY_BALANCED && large);
   // Small parts (decode-sized batches) measured 2% faster for combine, and

@@ -76,6 +76,22 @@ def test_units_match_oracle_and_persistent_split(T, H, E, R, k, payload, mask, s
     assert run.layout["status"] == again.layout["status"]
 
 
+@pytest.mark.parametrize("T,H,E,R,k", [
+    (32768, 8, 16, 4, 2), (32768, 512, 16, 4, 2), (32767, 512, 16, 4, 2), (32768, 256, 16, 4, 4),
+    (65536, 64, 16, 8, 1), (65600, 256, 16, 4, 3)])
+def test_many_narrow_rows(T, H, E, R, k):
+    """Sizes from which combine and the source-side sum leave the units for
+    the persistent split, and one token short of them."""
+    from test_gpu_dedup import _dedup_parity
+    from test_gpu_parity import _full_parity
+    cfg = wl.custom(T, H, E, R, k, zipf_s=1.2, seed=T + H + k)
+    inp = wl.make_inputs(cfg)
+    idx = wl.mask_slots(inp["topk_idx"], 0.1, seed=k)
+    delta = [-(r % 2) for r in range(R)]
+    _full_parity(cfg, inp, idx=idx, spare_rows=0, cap_delta=delta)
+    _dedup_parity(cfg, inp, idx=idx, spare_rows=0, pcap_delta=delta)
+
+
 # row widths of whole lines (fitting the last slice exactly, or not), of odd
 # multiples of 64 bytes and off the line; region bases by bytes past a line,
 # one after another over the regions
