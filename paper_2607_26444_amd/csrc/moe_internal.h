@@ -108,13 +108,17 @@ __host__ hipError_t launch_token_ranges(int64_t tokens, int slices, F&& launch) 
   return hipSuccess;
 }
 
-// Dynamic LDS that keeps at most `waves` wavefronts of a kernel with
-// wpb-wavefront workgroups (and no LDS of its own) resident on a compute
-// unit, 0 for no limit.  A compute unit has 160 KiB, allocated in granules of
-// 1280 bytes (128 of them).
+// Dynamic LDS per workgroup that limits the wavefronts of a kernel with
+// wpb-wavefront workgroups (and no LDS of its own) resident on a compute unit
+// to about `waves`, 0 for no limit.  A compute unit has 160 KiB, allocated in
+// granules of 1280 bytes (128 of them), and a workgroup takes the most granules
+// with which `waves` still fit; where that count of granules lets more in they
+// come too (workgroups of one: 12, 14, 16 and 18 as asked, 15 gives 16, 22
+// gives 25, 30 no limit).
 __host__ __forceinline__ unsigned wave_limit_lds(int waves, int wpb) {
   const int blocks = waves / wpb > 0 ? waves / wpb : 1;
-  return blocks * wpb >= 32 ? 0u : (unsigned)(128 / blocks * 1280);
+  const int granules = blocks < 128 ? 128 / blocks : 1;
+  return 128 / granules * wpb >= 32 ? 0u : (unsigned)(granules * 1280);
 }
 
 // Resident wavefronts per compute unit of the gathering unit kernels
