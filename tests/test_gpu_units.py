@@ -142,24 +142,61 @@ def test_rows_that_start_inside_a_line(T, H, E, R, k, payload, off_bases):
     _dedup_parity(cfg, inp, idx=idx)
 
 
+def _rows_equal(regions, x, src, k):
+    """Every region row is x's row of its slot, compared a few million at a time."""
+    at = 0
+    for r, n in enumerate(regions.rows):
+        rows = regions.region(r).view(torch.bfloat16)
+        for i in range(0, n, 1 << 22):
+            m = min(n - i, 1 << 22)
+            want = x[(src[at + i: at + i + m] // k).long()]
+            if not torch.equal(rows[i: i + m], want):
+                return False
+        at += n
+    return True
+
+
 def test_more_units_than_one_launch():
-    """2^24 + 5 one-slice tokens: the units go out in two launches.  k = 1 and
-    unit weights, so y is x bit for bit and every region row is its token's."""
+    """2^24 + 300 one-slice tokens: the units of every copy kernel go out in
+    two launches, the second one long enough for combine's XCD groups.  x holds
+    small integers and every weight is 1, so y is k * x and all sums are exact."""
     from paper_2607_26444_amd import moe
-    T, H, E, R = (1 << 24) + 5, 8, 4, 2
-    g = torch.Generator(device="cuda")
-    g.manual_seed(3)
-    idx = torch.randint(0, E, (T, 1), generator=g, device="cuda", dtype=torch.int32)
-    x = torch.randn(T, H, generator=g, device="cuda").to(torch.bfloat16)
-    lay = moe.Layout(T, 1, E, R)
+    T, H, E, R, k = (1 << 24) + 300, 64, 8, 4, 5
+    t = torch.arange(T, device="cuda", dtype=torch.int32)[:, None]
+    j = torch.arange(k, device="cuda", dtype=torch.int32)[None, :]
+    idx = ((t * 3 + t // 7 + j) % E).contiguous()
+    del t
+    x = torch.randint(-2, 3, (T, H), device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    w = torch.ones(T, k, device="cuda")
+    lay, dl = moe.Layout(T, k, E, R), moe.DedupLayout(T, k, E, R)
     lay.run(idx)
+    dl.run(idx)
+    src = lay.row_src
+    at = (moe.MOE_DTYPE_BF16, H, E, R, idx)
+
     reg = moe.Regions(lay.rank_count.tolist(), 2 * H, fill=0)
-    moe.moe_dispatch(x, None, moe.MOE_DTYPE_BF16, H, E, R, idx, lay.pos, lay.rank_offset,
-                     reg.table, None, reg.cap, lay.workspace, lay.status)
-    rows = torch.cat([reg.region(r).view(torch.bfloat16) for r in range(R)])
-    assert torch.equal(rows, x[lay.row_src.long()])
+    moe.moe_dispatch(x, None, *at, lay.pos, lay.rank_offset, reg.table, None, reg.cap,
+                     lay.workspace, lay.status)
+    assert _rows_equal(reg, x, src, k)
     y = torch.zeros_like(x)
-    moe.moe_combine(reg.table, torch.ones(T, 1, device="cuda"), H, E, R, idx, lay.pos,
-                    lay.rank_offset, reg.cap, y, lay.workspace, lay.status)
-    assert torch.equal(y, x)
-    assert int(lay.status) == 0
+    moe.moe_combine(reg.table, w, H, E, R, idx, lay.pos, lay.rank_offset, reg.cap, y,
+                    lay.workspace, lay.status)
+    assert torch.equal(y, k * x)
+
+    pairs = moe.Regions(dl.tok_count.tolist(), 2 * H, fill=0)
+    moe.moe_dispatch_dedup(x, None, *at, dl.tok_pos, dl.tok_offset, pairs.table, None, pairs.cap,
+                           dl.workspace, dl.status)
+    assert _rows_equal(pairs, x, dl.tok_src, k)
+    reg.buf.zero_()
+    moe.moe_expand(pairs.table, None, *at, lay.pos, lay.rank_offset, dl.tok_pos, dl.tok_offset,
+                   pairs.cap, reg.table, None, reg.cap, lay.workspace, lay.status)
+    assert _rows_equal(reg, x, src, k)
+    pairs.buf.zero_()
+    moe.moe_combine_local(reg.table, w, H, E, R, idx, lay.pos, lay.rank_offset, reg.cap,
+                          dl.tok_pos, dl.tok_offset, pairs.cap, pairs.table, lay.workspace,
+                          lay.status)
+    y.zero_()
+    moe.moe_combine_dedup(pairs.table, H, E, R, idx, dl.tok_pos, dl.tok_offset, pairs.cap, y,
+                          dl.workspace, dl.status)
+    assert torch.equal(y, k * x)
+    assert int(lay.status) == 0 and int(dl.status) == 0
