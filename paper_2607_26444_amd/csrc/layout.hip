@@ -538,7 +538,7 @@ __global__ __launch_bounds__(kBlock) void layout_place_kernel(
       rank_offset[R] = FIXED ? E * C : (int32_t)n_total;
       bound[0] = 0;
     }
-    // work tickets of dispatch and combine (and a spare group): {next, done} of every shard
+    // work tickets of dispatch and combine: {next, done} of every shard
     if (tid < kTicketGroups * 16 * 2)   // every line a group can hold
       tickets[(tid >> 1) * kTicketStride + (tid & 1)] = 0u;
     for (int r = tid; r < R; r += kBlock) {

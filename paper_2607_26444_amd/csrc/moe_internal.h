@@ -27,7 +27,7 @@ struct LayoutGeom {
   int nc;
   int ncp;              // row pitch of the count matrix: E rounded up to 4
   size_t plan_bytes;    // bound[MOE_PLAN_PARTS + 1], padded to 256 bytes
-  size_t ticket_offset; // work tickets: kTicketBlockBytes (three sharded groups, see below)
+  size_t ticket_offset; // work tickets: kTicketBlockBytes (two sharded groups, see below)
   size_t gen_offset;    // uint64 generation word of the one-launch layout (end of that block)
   size_t counts_offset;
   size_t counts_bytes;  // int32 [nc][ncp], chunk-major
@@ -313,7 +313,7 @@ __device__ __forceinline__ int waves_in_shard(int s, int W) {
   return n;
 }
 constexpr int kTicketGroupWords = 16 * kTicketStride;              // 2 KiB per kernel (<= 16 shards)
-constexpr int kTicketGroups = 3;                                   // dispatch, combine, one spare
+constexpr int kTicketGroups = 2;                                   // dispatch, combine
 constexpr size_t kTicketBlockBytes = 8192;                         // groups + generation word
 static_assert(kTicketGroups * kTicketGroupWords * 4 + 128 <= (int)kTicketBlockBytes, "tickets");
 

@@ -140,11 +140,11 @@ class GpuRun:
 
 
 # The work tickets sit right after the plan, which is bound[MOE_PLAN_PARTS +
-# 1] padded to 256 bytes (the library's internal workspace layout): three
-# groups (dispatch, combine, expand) of 16 shards, each shard {next claim,
-# wavefronts done} at the start of its own 128-byte line.
+# 1] padded to 256 bytes (the library's internal workspace layout): two groups
+# (dispatch, combine) of 16 shards, each shard {next claim, wavefronts done} at
+# the start of its own 128-byte line.
 TICKET_OFFSET = ((moe.MOE_PLAN_PARTS + 1) * 4 + 255) // 256 * 256
-TICKET_LINES = 3 * 16
+TICKET_LINES = 2 * 16
 TICKET_BYTES = TICKET_LINES * 128
 
 
