@@ -1,5 +1,6 @@
-"""Build libmoe.so (HIP, gfx950) in-tree with hipcc, and _moecall.so, the
-native argument marshalling of the Python binding, with the host compiler.
+"""Build libmoe.so (HIP, gfx950) in-tree with hipcc, and _moecall, the native
+argument marshalling of the Python binding, with the host compiler for the
+running interpreter (whose ABI tag its file name carries).
 
 python -m paper_2607_26444_amd.build [--isa DIR]
 
@@ -21,7 +22,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libmoe.so")
-PYCALL = os.path.join(HERE, "_moecall.so")
+PYCALL = os.path.join(HERE, "_moecall" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["api.hip", "layout.hip", "dispatch.hip", "combine.hip", "expert.hip", "dedup.hip",
            "scratch.hip"]
 
@@ -59,6 +60,9 @@ def build_pycall(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(PYCALL + ".tmp", PYCALL)
+    untagged = os.path.join(HERE, "_moecall.so")   # any interpreter would take it
+    if os.path.exists(untagged):
+        os.remove(untagged)
     return PYCALL
 
 

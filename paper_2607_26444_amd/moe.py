@@ -5,13 +5,14 @@ tensors and the current HIP stream to the C entry point of the same name;
 all work runs in the library's kernels.  The calls of a batch go through the
 native marshalling of csrc/pycall.cpp, the others through ctypes.  torch is
 imported before the library is loaded so that both use the one HIP runtime
-already in the process.  There is no fallback: without libmoe.so and
-_moecall.so every call raises.
+already in the process.  There is no fallback: without libmoe.so every call raises, and
+without a _moecall built for the running interpreter every call of a batch.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import sys
 
 import torch
 
@@ -117,7 +118,7 @@ _fast = None
 
 
 def _calls():
-    """The native marshalling (_moecall.so), bound to the loaded library."""
+    """The native marshalling (_moecall), bound to the loaded library."""
     global _fast
     if _fast is None:
         lib()
@@ -125,8 +126,8 @@ def _calls():
             from . import _moecall
         except ImportError as e:
             raise RuntimeError(
-                f"{os.path.join(HERE, '_moecall.so')} cannot be loaded: build it with "
-                "`python -m paper_2607_26444_amd.build` (no fallback exists)") from e
+                f"no _moecall for this interpreter (Python {sys.version.split()[0]}) in {HERE}: "
+                "build it with `python -m paper_2607_26444_amd.build` (no fallback exists)") from e
         _moecall.init(LIB_PATH, ctypes.ArgumentError, torch._C._cuda_getDevice,
                       torch._C._cuda_getCurrentRawStream)
         _fast = _moecall

@@ -1,117 +1,222 @@
-"""The native marshalling hands every argument to the right place: for calls
-that the library refuses before any launch, it returns the code that the same
-call through ctypes returns, whichever argument is the wrong one."""
+"""The native marshalling hands every argument to the right place.
+
+A stand-in library that exports the entry points of moe.h and records what it
+is called with takes the place of libmoe.so behind the binding: every wrapper is
+called by keyword with a value of its own for each name, and each C parameter
+must arrive with the value of its name in moe.h's prototypes.  Nothing is
+launched, so this runs without a GPU."""
 import ctypes
+import inspect
+import os
+import re
+import subprocess
+import sys
 
 import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2607_26444_amd import moe  # noqa: E402
+from paper_2607_26444_amd import build, moe  # noqa: E402
+
+NAMES = ("moe_layout", "moe_layout_fixed", "moe_dispatch", "moe_combine", "moe_layout_dedup",
+         "moe_dispatch_dedup", "moe_expand", "moe_combine_local", "moe_combine_dedup")
+
+
+def prototypes():
+    """C parameters (type, name) of each entry point, from the header."""
+    text = re.sub(r"/\*.*?\*/", "", open(os.path.join(build.INCLUDE, "moe.h")).read(), flags=re.S)
+    out = {}
+    for name in NAMES:
+        args = re.search(rf"\bint {name}\(([^)]*)\);", text).group(1)
+        out[name] = [re.match(r"(.*?)(\w+)$", " ".join(a.split())).groups()
+                     for a in args.split(",")]
+    return out
+
+
+PROTO = prototypes()
 
 
 class Buf:
     """Stands in for a device tensor; its address is never followed."""
     is_cuda = True
 
-    def __init__(self, addr=1 << 20, nbytes=1 << 30, shape=None):
-        self.addr, self.nbytes, self.shape = addr, nbytes, shape
+    def __init__(self, addr, shape=None):
+        self.addr, self.shape = addr, shape
 
     def data_ptr(self):
         return self.addr
 
     def numel(self):
-        return self.nbytes
+        return self.addr // 16 + 3
 
     def element_size(self):
-        return 1
+        return 4
 
 
 class Stream:
-    cuda_stream = 0
+    cuda_stream = 0x7F00DEADB000
 
 
-IDX = Buf(shape=(0, 2))     # T = 0: nothing is launched by the copy calls
-E, R, H = 16, 4, 256
-BAD = {"null": None, "odd": Buf((1 << 20) + 4), "small": Buf(nbytes=64), "float": 1.5,
-       "big": 1 << 40, "minus": -1, "zero": 0, "three": 3,
-       "T": Buf(shape=(5, 2)), "k": Buf(shape=(5, 99))}
-
-# name, arguments in order (tensors b, integers, the index table, workspace w)
-b, w, s = Buf(), Buf(), Stream()
-CALLS = {
-    "moe_layout": [IDX, E, R, b, b, b, b, b, b, w, b, s],
-    "moe_layout_fixed": [IDX, E, R, 4, b, b, b, b, b, b, w, b, s],
-    "moe_dispatch": [b, None, 0, H, E, R, IDX, b, b, b, None, b, w, b, s, 0],
-    "moe_combine": [b, b, H, E, R, IDX, b, b, b, b, w, b, s],
-    "moe_layout_dedup": [IDX, E, R, b, b, b, b, w, b, s],
-    "moe_dispatch_dedup": [b, b, 1, H, E, R, IDX, b, b, b, b, b, w, b, s, 0],
-    "moe_expand": [b, None, 0, H, E, R, IDX, b, b, b, b, b, b, None, b, w, b, s, 0],
-    "moe_combine_local": [b, b, H, E, R, IDX, b, b, b, b, b, b, b, w, b, s],
-    "moe_combine_dedup": [b, H, E, R, IDX, b, b, b, b, w, b, s],
-}
-# position of scale_pitch in the C call, which Python passes last
-PITCH = {"moe_dispatch": 13, "moe_dispatch_dedup": 13, "moe_expand": 16}
+# a value of its own for every integer name; T past 32 bits
+INTEGERS = dict(dtype=1, H=7176, E=257, R=63, capacity=4099, scale_pitch=260)
+T, K = (1 << 33) + 5, 31
 
 
-def through_ctypes(name, args):
-    """The C argument list by its documented order: pointers for tensors, T
-    (and H where the call has one) and k around the table, the workspace's
-    bytes after it."""
-    ptr = moe._ptr
-    args = list(args)
-    pitch = args.pop() if name in PITCH else None
-    stream, status, work = args.pop(), args.pop(), args.pop()
-    idx = next(a for a in args if isinstance(a, Buf) and a.shape)
-    T, k = idx.shape
-    out, at = [], args.index(idx)
-    head, tail = args[:at], args[at + 1:]
-    if name.startswith("moe_layout"):
-        out = [ptr(idx), T, k] + [a if isinstance(a, (int, float)) else ptr(a) for a in tail]
-    else:
-        h, e, r = head[-3:]
-        out = [a if isinstance(a, (int, float)) else ptr(a) for a in head[:-3]]
-        out += [T, h, k, e, r, ptr(idx)]
-        out += [a if isinstance(a, (int, float)) else ptr(a) for a in tail]
-    if pitch is not None:
-        out.insert(PITCH[name], pitch)
-    out += [ptr(work), work.nbytes if work else 0, ptr(status), stream.cuda_stream]
-    return getattr(moe.lib(), name)(*out)
+def arguments(name):
+    """{parameter of the wrapper: value}, tensors at distinct addresses."""
+    args = {}
+    for i, p in enumerate(inspect.signature(getattr(moe, name)).parameters):
+        if p in INTEGERS:
+            args[p] = INTEGERS[p]
+        elif p == "stream":
+            args[p] = Stream()
+        else:
+            args[p] = Buf(0x7F0000000000 + 0x1000 * (i + 1), (T, K) if p == "topk_idx" else None)
+    return args
 
 
-def native(name, args):
-    return getattr(moe._calls(), name[4:])(*args)
+def expected(name, args):
+    """What each C parameter must be, by its name in the header."""
+    out = []
+    for ctype, p in PROTO[name]:
+        if p == "T":
+            out.append(T)
+        elif p == "k":
+            out.append(K)
+        elif p == "workspace_bytes":
+            w = args["workspace"]
+            out.append(w.numel() * w.element_size())
+        elif p == "stream":
+            out.append(args[p].cuda_stream)
+        else:
+            v = args[p]
+            assert ("*" in ctype) == (v is None or isinstance(v, Buf)), (name, p)
+            out.append(0 if v is None else v.addr if isinstance(v, Buf) else v)
+    return out
 
 
-CASES = [(n, i, k) for n, a in CALLS.items() for i in range(len(a)) for k in BAD
-         if a[i] is not s and not (a[i] is w and k == "null")   # a workspace has a size
-         and ((k in ("null", "odd", "small") and isinstance(a[i], Buf) and a[i] is not IDX)
-              or (k in ("T", "k") and a[i] is IDX)
-              or (k in ("big", "minus", "zero", "three") and isinstance(a[i], int)))]
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    """The recording library, bound behind the wrappers for this module."""
+    d = tmp_path_factory.mktemp("stub")
+    src, so = os.path.join(d, "stub.cpp"), os.path.join(d, "libstub.so")
+    with open(src, "w") as f:
+        f.write('#include "moe.h"\nextern "C" { unsigned long long rec[32]; int n_rec, code; }\n')
+        for name, params in PROTO.items():
+            f.write(f'extern "C" int {name}({", ".join(t + p for t, p in params)}) {{\n  n_rec = 0;\n')
+            f.write("".join(f"  rec[n_rec++] = (unsigned long long){p};\n" for _, p in params))
+            f.write("  return code;\n}\n")
+    subprocess.run(["g++", "-shared", "-fPIC", "-I", build.INCLUDE, src, "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    calls = moe._calls()
+    seen = []
+
+    def get_stream(device):
+        seen.append(device)
+        return Stream.cuda_stream + 0x40
+    calls.init(so, ctypes.ArgumentError, lambda: 3, get_stream)
+
+    class Stub:
+        code = ctypes.c_int.in_dll(lib, "code")
+        streams = seen
+
+        @staticmethod
+        def recorded():
+            n = ctypes.c_int.in_dll(lib, "n_rec").value
+            return list((ctypes.c_ulonglong * 32).in_dll(lib, "rec"))[:n]
+
+    yield Stub
+    calls.init(moe.LIB_PATH, ctypes.ArgumentError, torch._C._cuda_getDevice,
+               torch._C._cuda_getCurrentRawStream)
 
 
-@pytest.mark.parametrize("name,at,kind", CASES)
-def test_same_code_as_ctypes(name, at, kind):
-    args = list(CALLS[name])
-    args[at] = BAD[kind]
-    if kind == "T":     # tokens: refuse the batch by its experts, launch nothing
-        args[args.index(BAD["T"]) + 1 if name.startswith("moe_layout")
-             else args.index(BAD["T"]) - 1] = 5
-    elif name.startswith("moe_layout"):   # T = 0 still launches: refuse it by R
-        args[2] = 5
-    want = through_ctypes(name, args)
-    assert native(name, args) == want
-    if kind in ("T", "k") or name.startswith("moe_layout"):
-        assert want == moe.MOE_EINVAL
+@pytest.mark.parametrize("name", NAMES)
+def test_every_argument_arrives(stub, name):
+    args = arguments(name)
+    getattr(moe, name)(**args)
+    assert stub.recorded() == expected(name, args)
 
 
-def test_wrong_python_arguments():
+@pytest.mark.parametrize("name", NAMES)
+def test_none_is_null_for_every_pointer(stub, name):
+    for p, v in arguments(name).items():
+        if not isinstance(v, Buf) or p in ("topk_idx", "workspace"):
+            continue   # these two have a size, and so are not optional
+        args = arguments(name)
+        args[p] = None
+        getattr(moe, name)(**args)
+        assert stub.recorded() == expected(name, args), p
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_no_stream_is_the_current_one(stub, name):
+    args = arguments(name)
+    del args["stream"]
+    stub.streams.clear()
+    getattr(moe, name)(**args)
+    at = [p for _, p in PROTO[name]].index("stream")
+    assert stub.recorded()[at] == Stream.cuda_stream + 0x40 and stub.streams == [3]
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_return_code_becomes_the_error(stub, name):
+    stub.code.value = moe.MOE_EALIGN
+    try:
+        with pytest.raises(moe.MoeError, match=name) as e:
+            getattr(moe, name)(**arguments(name))
+    finally:
+        stub.code.value = 0
+    assert e.value.code == moe.MOE_EALIGN
+
+
+def test_scale_pitch_defaults_to_packed(stub):
+    for name in ("moe_dispatch", "moe_dispatch_dedup", "moe_expand"):
+        args = arguments(name)
+        del args["scale_pitch"]
+        getattr(moe, name)(**args)
+        assert stub.recorded() == expected(name, dict(args, scale_pitch=0)), name
+
+
+def test_integers_as_ctypes_takes_them(stub):
+    for given, got in ((ctypes.c_int(40), 40), (True, 1), (torch.tensor(9), 9), (-1, 2 ** 64 - 1),
+                       (1 << 40, 0)):
+        args = dict(arguments("moe_combine"), H=given)
+        moe.moe_combine(**args)
+        at = [p for _, p in PROTO["moe_combine"]].index("H")
+        assert stub.recorded()[at] == got, given
+
+
+def test_wrong_python_arguments(stub):
+    def call(**change):
+        moe.moe_combine(**dict(arguments("moe_combine"), **change))
     with pytest.raises(ctypes.ArgumentError):
-        moe.moe_combine(b, b, 1.5, E, R, IDX, b, b, b, b, w, b, s)
+        call(H=1.5)
+    with pytest.raises(ctypes.ArgumentError):
+        call(E=None)
     with pytest.raises(ValueError, match="device tensors"):
-        moe.moe_combine(torch.zeros(1), b, H, E, R, IDX, b, b, b, b, w, b, s)
+        call(y=torch.zeros(1))
     with pytest.raises(ValueError):
-        moe.moe_layout(Buf(shape=(4,)), E, R, b, b, b, b, b, b, w, b, s)
+        call(topk_idx=Buf(64, (4,)))
     with pytest.raises(AttributeError):
-        moe.moe_combine(b, b, H, E, R, IDX, b, b, b, b, None, b, s)
-    assert native("moe_combine", [b, b, ctypes.c_int(H), E, R, IDX, b, b, b, b, w, b, s]) == 0
+        call(workspace=None)
+    with pytest.raises(AttributeError):
+        call(topk_idx=None)
+    with pytest.raises(TypeError):
+        moe._calls().combine(1, 2)
+
+
+def test_other_interpreters_extension_is_not_taken(tmp_path):
+    """The extension's name carries the interpreter's ABI tag: one built for
+    another interpreter is not loaded, and the error says what to build."""
+    assert os.path.exists(build.PYCALL) and ".cpython-" in os.path.basename(build.PYCALL)
+    assert not os.path.exists(os.path.join(build.HERE, "_moecall.so"))
+    pkg = tmp_path / "paper_2607_26444_amd"
+    pkg.mkdir()
+    for f in ("__init__.py", "moe.py", "libmoe.so"):
+        os.symlink(os.path.join(build.HERE, f), pkg / f)
+    os.symlink(build.PYCALL, pkg / "_moecall.cpython-399-x86_64-linux-gnu.so")
+    run = subprocess.run([sys.executable, "-c", "from paper_2607_26444_amd import moe; moe._calls()"],
+                         cwd=tmp_path, capture_output=True, text=True,
+                         env=dict(os.environ, PYTHONPATH=str(tmp_path)))
+    assert run.returncode != 0
+    assert "RuntimeError: no _moecall for this interpreter" in run.stderr
