@@ -29,6 +29,7 @@ PyObject* s_shape;
 PyObject* s_cuda_stream;
 PyObject* s_value;
 PyObject* g_argument_error;   // ctypes.ArgumentError
+PyObject* g_c_int;            // ctypes.c_int
 PyObject* g_get_device;       // () -> index of the current device
 PyObject* g_get_stream;       // (index) -> address of its current stream
 
@@ -53,17 +54,15 @@ class Args {
     }
   }
 
-  // An integer as ctypes' c_int / c_long take it: anything with __index__,
-  // or a ctypes integer.
+  // An integer as a ctypes c_int parameter takes it: anything with __index__,
+  // or a c_int.
   unsigned long long integer(PyObject* o) {
     if (PyLong_CheckExact(o)) return PyLong_AsUnsignedLongLongMask(o);
     PyObject* v = nullptr;
-    if (PyIndex_Check(o)) {
+    if (PyIndex_Check(o))
       v = PyNumber_Index(o);
-    } else {
+    else if (PyObject_IsInstance(o, g_c_int) == 1)
       v = PyObject_GetAttr(o, s_value);
-      if (v && !PyLong_Check(v)) Py_CLEAR(v);
-    }
     if (!v) {
       PyErr_Clear();
       PyErr_Format(g_argument_error, "TypeError: wrong type %.100s", Py_TYPE(o)->tp_name);
@@ -347,12 +346,12 @@ PyObject* combine_dedup(PyObject*, PyObject* const* args, Py_ssize_t n) {
   });
 }
 
-// init(lib_path, argument_error, get_device, get_stream): binds the entry
-// points of the libmoe.so that is already loaded.
+// init(lib_path, argument_error, c_int, get_device, get_stream): binds the
+// entry points of the libmoe.so that is already loaded.
 PyObject* init(PyObject*, PyObject* args) {
   const char* path;
-  PyObject *err, *dev, *stream;
-  if (!PyArg_ParseTuple(args, "sOOO", &path, &err, &dev, &stream)) return nullptr;
+  PyObject *err, *c_int, *dev, *stream;
+  if (!PyArg_ParseTuple(args, "sOOOO", &path, &err, &c_int, &dev, &stream)) return nullptr;
   void* h = dlopen(path, RTLD_NOW | RTLD_NOLOAD);
   if (!h) {
     PyErr_Format(PyExc_RuntimeError, "%s is not loaded", path);
@@ -368,6 +367,8 @@ PyObject* init(PyObject*, PyObject* args) {
 #undef X
   Py_INCREF(err);
   Py_XSETREF(g_argument_error, err);
+  Py_INCREF(c_int);
+  Py_XSETREF(g_c_int, c_int);
   Py_INCREF(dev);
   Py_XSETREF(g_get_device, dev);
   Py_INCREF(stream);

@@ -128,7 +128,7 @@ def _calls():
             raise RuntimeError(
                 f"no _moecall for this interpreter (Python {sys.version.split()[0]}) in {HERE}: "
                 "build it with `python -m paper_2607_26444_amd.build` (no fallback exists)") from e
-        _moecall.init(LIB_PATH, ctypes.ArgumentError, torch._C._cuda_getDevice,
+        _moecall.init(LIB_PATH, ctypes.ArgumentError, ctypes.c_int, torch._C._cuda_getDevice,
                       torch._C._cuda_getCurrentRawStream)
         _fast = _moecall
     return _fast

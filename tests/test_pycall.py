@@ -114,7 +114,7 @@ def stub(tmp_path_factory):
     def get_stream(device):
         seen.append(device)
         return Stream.cuda_stream + 0x40
-    calls.init(so, ctypes.ArgumentError, lambda: 3, get_stream)
+    calls.init(so, ctypes.ArgumentError, ctypes.c_int, lambda: 3, get_stream)
 
     class Stub:
         code = ctypes.c_int.in_dll(lib, "code")
@@ -126,7 +126,7 @@ def stub(tmp_path_factory):
             return list((ctypes.c_ulonglong * 32).in_dll(lib, "rec"))[:n]
 
     yield Stub
-    calls.init(moe.LIB_PATH, ctypes.ArgumentError, torch._C._cuda_getDevice,
+    calls.init(moe.LIB_PATH, ctypes.ArgumentError, ctypes.c_int, torch._C._cuda_getDevice,
                torch._C._cuda_getCurrentRawStream)
 
 
@@ -193,6 +193,12 @@ def test_wrong_python_arguments(stub):
         call(H=1.5)
     with pytest.raises(ctypes.ArgumentError):
         call(E=None)
+
+    class Value:
+        value = 5
+    for other in (ctypes.c_long(3), ctypes.c_bool(True), Value()):   # not a c_int
+        with pytest.raises(ctypes.ArgumentError):
+            call(R=other)
     with pytest.raises(ValueError, match="device tensors"):
         call(y=torch.zeros(1))
     with pytest.raises(ValueError):
