@@ -149,13 +149,9 @@ def test_dedup_full_size(name):
              f"({n_pairs / (cfg['T'] * cfg['k']):.3f})")
 
 
-def test_dedup_large_batch_claims_every_part():
-    """24576 tokens of 14 KiB: the pair-row calls' parts carry ~140 KiB, so
-    their default split hands every part out at run time."""
-    cfg = wl.custom(24576, 7168, 256, 64, 8, zipf_s=1.2, seed=24576)
-    T, H, k = cfg["T"], cfg["H"], cfg["k"]
-    assert T * 2 * H * (1 + (k + 1) // 2) // moe.MOE_PLAN_PARTS >= 128 << 10
-    _dedup_parity(cfg)
+def test_dedup_large_batch():
+    """24576 tokens of 14 KiB, the largest chain that is compared whole."""
+    _dedup_parity(wl.custom(24576, 7168, 256, 64, 8, zipf_s=1.2, seed=24576))
 
 
 @pytest.mark.parametrize("T,H,E,R,k,zipf,signed_w", [

@@ -120,6 +120,7 @@ def test_custom_shapes(T, H, E, R, k, payload, mask):
     _full_parity(cfg, inp, idx=idx)
 
 
+@pytest.mark.parametrize("cpolicy", [0, 4])   # the units; persistent wavefronts
 @pytest.mark.parametrize("T,H,E,R,k,mask,cap", [
     (300, 4104, 32, 8, 2, 0.1, False),    # 8 KiB + 16 B: one lane in the last segment
     (257, 6152, 64, 16, 4, 0.2, True),    # 12 KiB + 16 B, capacity drops
@@ -128,10 +129,10 @@ def test_custom_shapes(T, H, E, R, k, payload, mask):
     (200, 4096, 64, 16, 8, 0.1, False),   # 8 KiB: segment-by-segment path, just below
     (200, 8200, 64, 16, 8, 0.1, False),   # 16 KiB + 16 B: segment-by-segment, just above
 ])
-def test_combine_row_widths(T, H, E, R, k, mask, cap):
-    """Combine output rows around the widths that are reduced into registers
-    and stored as one burst (more than 8, at most 16 KiB): ragged last
-    segments, masked and capacity-dropped slots, both neighbours."""
+def test_combine_row_widths(T, H, E, R, k, mask, cap, cpolicy):
+    """Combine output rows around the widths that the persistent kernel reduces
+    into registers and stores as one burst (at least 8, at most 16 KiB): ragged
+    last segments, masked and capacity-dropped slots, both neighbours."""
     cfg = wl.custom(T, H, E, R, k, zipf_s=1.2, seed=T + H + k)
     inp = wl.make_inputs(cfg)
     idx = wl.mask_slots(inp["topk_idx"], mask, seed=T) if mask else None
@@ -139,7 +140,7 @@ def test_combine_row_widths(T, H, E, R, k, mask, cap):
     if cap:
         delta = [0] * R
         delta[0] = -7
-    _full_parity(cfg, inp, idx=idx, cap_delta=delta, spare_rows=1)
+    _full_parity(cfg, inp, idx=idx, cap_delta=delta, spare_rows=1, combine_policy=cpolicy)
 
 
 @pytest.mark.parametrize("pitch", [0, 116, 128, 256])
@@ -191,8 +192,9 @@ def test_dynamic_policy_matches_oracle(T, H, E, R, k, payload, mask):
     inp = wl.make_inputs(cfg)
     idx = wl.mask_slots(inp["topk_idx"], mask, seed=T) if mask else None
     _full_parity(cfg, inp, idx=idx, policy=3, combine_policy=3, repeat=3)
-    # the default split hands out its second half at run time: same reset
-    _full_parity(cfg, inp, idx=idx, policy=0, combine_policy=0, repeat=3)
+    # byte-balanced parts at a wavefront count that hands out the second half
+    # at run time: same reset
+    _full_parity(cfg, inp, idx=idx, policy=0, combine_policy=0, repeat=3, waves=256)
 
 
 @pytest.mark.parametrize("policy,cpolicy", [(0, 0), (1, 0), (2, 0), (3, 3), (4, 4)])
@@ -368,19 +370,27 @@ def test_decode_workload_full():
 def test_full_size_workloads(name):
     """Full-size workloads against the whole oracle chain: layout, plan,
     dispatch and the stand-in expert bit-exact, and combine within the
-    tolerance on every token.  Dispatch and combine run twice on one layout
-    (at these sizes the default split claims parts at run time, so the
-    second call relies on the first one's counter reset; the outputs are
-    reset to the sentinel in between).  For bf16 payloads, unit weights on
-    the dispatched rows themselves must also give exactly bf16(k*x) for
-    every token."""
+    tolerance on every token.  The same with wavefront counts at which both
+    explicit splits claim every part at run time, twice on one layout (the
+    second call relies on the first one's counter reset; the outputs are reset
+    to the sentinel in between): the same bytes.  For bf16 payloads, unit
+    weights on the dispatched rows themselves must also give exactly bf16(k*x)
+    for every token."""
     h = _h()
     cfg = wl.get(name)
     inp = wl.make_inputs(cfg)
     k = cfg["k"]
     h.log(f"[full] {cfg['name']}")
-    run, ref = _full_parity(cfg, inp, spare_rows=1, repeat=2)
+    run, ref = _full_parity(cfg, inp, spare_rows=1)
     assert run.layout["status"] == 0
+    rb = wl.row_bytes(cfg)
+    assert cfg["T"] * rb * (1 + k) // 12288 >= 64 << 10          # dispatch's parts: all claimed
+    assert cfg["T"] * 2 * cfg["H"] * (1 + k) // 12288 >= 128 << 10   # combine's
+    again = h.GpuRun(cfg, inp, spare_rows=1, repeat=2, waves=512)
+    for r in range(cfg["R"]):
+        assert torch.equal(run.regions.region(r), again.regions.region(r)), r
+    assert np.array_equal(run.y, again.y)
+    del again
     h.log(f"[full] {cfg['name']}: layout, plan, dispatch, expert bit-exact; "
           f"combine within tolerance on all {cfg['T']} tokens")
     del ref

@@ -86,8 +86,8 @@ N_LARGE_CASES = 4
 
 
 def _large_shape(seed):
-    """A random batch large enough that the default split hands every part
-    out at run time (a plan part carries at least 128 KiB on average)."""
+    """A random batch large enough that byte-balanced parts are claimed at run
+    time (a plan part carries at least 128 KiB on average)."""
     rng = np.random.default_rng(3000 + seed)
     R = int(rng.choice([16, 32, 64]))
     E = R * int(rng.choice([2, 4]))
@@ -104,6 +104,9 @@ def _large_shape(seed):
 
 @pytest.mark.parametrize("seed", range(N_LARGE_CASES))
 def test_random_large_batch_matches_oracle(seed):
+    """The default against the oracle; byte-balanced parts, claimed, twice on one
+    layout, against the default bit for bit."""
+    import gpu_harness as h
     from test_gpu_parity import _full_parity
     s = _large_shape(seed)
     cfg = wl.custom(s["T"], s["H"], s["E"], s["R"], s["k"],
@@ -111,4 +114,8 @@ def test_random_large_batch_matches_oracle(seed):
                     seed=7000 + seed)
     inp = wl.make_inputs(cfg)
     idx = wl.mask_slots(inp["topk_idx"], s["mask"], seed=seed) if s["mask"] else None
-    _full_parity(cfg, inp, idx=idx, repeat=2, spare_rows=1)
+    run, _ = _full_parity(cfg, inp, idx=idx, spare_rows=1)
+    again = h.GpuRun(cfg, inp, topk_idx=idx, repeat=2, spare_rows=1, waves=(512, 1024)[seed % 2])
+    for r in range(cfg["R"]):
+        assert torch.equal(run.regions.region(r), again.regions.region(r)), r
+    assert np.array_equal(run.y, again.y)

@@ -45,21 +45,23 @@ def _read_device(ptr, nbytes):
 
 def _step(h, moe, cfg, inp, idx_d, w_d, x_d, lay_out, ws, caps):
     """dispatch -> stand-in expert -> combine of one batch with the given
-    layout outputs and workspace; returns (regions, y)."""
+    layout outputs and workspace, parts of the workspace's plan claimed at run
+    time from its tickets; returns (regions, y)."""
     T, H, E, R, k = cfg["T"], cfg["H"], cfg["E"], cfg["R"], cfg["k"]
     rows = [int(c) for c in caps]
     regions = moe.Regions(rows, wl.row_bytes(cfg), guard_bytes=h.GUARD, fill=h.SENTINEL)
     eregions = moe.Regions(rows, 2 * H, guard_bytes=h.GUARD, fill=h.SENTINEL)
     cap_d = h.to_dev(caps)
     y = torch.full((T, H), 0x5A5A, dtype=torch.int16, device="cuda")
-    moe.moe_dispatch(x_d, None, moe.MOE_DTYPE_BF16, H, E, R, idx_d, lay_out["pos"],
-                     lay_out["rank_offset"], regions.table, None, cap_d, ws,
-                     lay_out["status"])
+    moe.moe_dispatch_ex(x_d, None, moe.MOE_DTYPE_BF16, H, E, R, idx_d, lay_out["pos"],
+                        lay_out["rank_offset"], None, regions.table, None, cap_d, ws,
+                        lay_out["status"], policy=moe.MOE_POLICY_DYNAMIC)
     moe.moe_expert_scale(regions.table, None, moe.MOE_DTYPE_BF16, H, E, R, False,
                          lay_out["expert_offset"], lay_out["rank_offset"], cap_d,
                          eregions.table, T * k)
-    moe.moe_combine(eregions.table, w_d, H, E, R, idx_d, lay_out["pos"],
-                    lay_out["rank_offset"], cap_d, y, ws, lay_out["status"])
+    moe.moe_combine_ex(eregions.table, w_d, H, E, R, idx_d, lay_out["pos"],
+                       lay_out["rank_offset"], cap_d, y, ws, lay_out["status"],
+                       policy=moe.MOE_POLICY_DYNAMIC)
     torch.cuda.synchronize()
     return regions, y.cpu().numpy().view(np.uint16)
 
@@ -71,7 +73,7 @@ def test_layout_scratch_matches_layout_twice():
     import gpu_harness as h
     from paper_2607_26444_amd import moe
     shapes = [
-        # parts of >= 128 KiB: dispatch and combine claim every part
+        # a large batch: 48 layout chunks
         dict(T=12288, H=7168, E=256, R=64, k=8, zipf=1.2, mask=0.0),
         # smaller batch: the single-workgroup layout, masked slots
         dict(T=200, H=1032, E=32, R=8, k=4, zipf=0.0, mask=0.1),
