@@ -189,6 +189,12 @@ constexpr int kMaxExpertsPerThread = MOE_MAX_EXPERTS / kBlock;  // 4
 constexpr int kCountBatch = 16;      // 16-byte count loads in flight per thread
 constexpr int kMaxCountGroups = 16;  // count-matrix rows read side by side
 
+// How the unfilled rows of fixed windows are shared out: groups of 2^lg
+// threads, `share` groups to a window.
+struct WindowFill {
+  int lg, share;
+};
+
 // How layout_place_kernel learns the per-chunk counts.
 //   kPlaceAfterCount  a layout_count launch left the count matrix
 //   kPlaceSingle      one workgroup holds the whole batch (T <= kBlock): the
@@ -331,7 +337,8 @@ __global__ __launch_bounds__(kBlock) void layout_place_kernel(
     int32_t* __restrict__ expert_offset, int32_t* __restrict__ rank_count,
     int32_t* __restrict__ rank_offset, int32_t* __restrict__ pos,
     int32_t* __restrict__ row_src, int32_t* __restrict__ bound, uint32_t* __restrict__ tickets,
-    uint32_t* __restrict__ status, uint64_t* gen, uint64_t* flags, uint64_t sync_ticks) {
+    uint32_t* __restrict__ status, uint64_t* gen, uint64_t* flags, uint64_t sync_ticks,
+    WindowFill fill) {
   constexpr bool SINGLE = MODE == kPlaceSingle;
   extern __shared__ __align__(16) unsigned char smem[];
   uint64_t* mask = reinterpret_cast<uint64_t*>(smem);               // [4][E]
@@ -656,26 +663,26 @@ __global__ __launch_bounds__(kBlock) void layout_place_kernel(
 
   if (FIXED) {
     // Window rows no slot fills have no source: rows [e*C + placed_e,
-    // (e+1)*C) of every expert.  A window goes to a group of neighbouring
-    // threads: the power of two that covers it up to one wavefront, several
-    // wavefronts of the grid where there are more of them than windows.  The
-    // groups take the windows in turn, so wide windows are written as runs
-    // and narrow ones side by side.  256 experts, us of the layout with one
-    // workgroup per window at a time -> with all window rows strided over the
-    // grid's threads, an LDS lookup per row -> now: 64 tokens, 16 rows 33.0
-    // 9.3 9.4; 256 tokens, 4096 rows 158 507 119; 32768 tokens, 8192 rows 16.1
-    // 23.0 16.6.
-    int g = 1;
-    while (g < C && g < kWave) g *= 2;
-    const int groups = nc * (kBlock / g), id = (c * kBlock + tid) / g;
-    const int share = max(1, min(groups / E, (C + g - 1) / g));   // groups per window
-    const int windows = groups / share;                           // at a time
-    const int step = share * g, in = id % share * g + tid % g;
-    if (id < windows * share)
-      for (int e = id / share; e < E; e += windows) {
-        const int placed = eoff[e + 1] - eoff[e];
-        for (int64_t i = placed + in; i < C; i += step) row_src[(int64_t)e * C + i] = -1;
-      }
+    // (e+1)*C) of every expert.  A window goes to groups of neighbouring
+    // threads (window_fill), which take the windows in turn, so wide windows
+    // are written as runs and narrow ones side by side.  256 experts, us of the
+    // layout with one workgroup per window at a time -> with all window rows
+    // strided over the grid's threads, an LDS lookup per row -> now: 64 tokens,
+    // 16 rows 33.0 9.4 9.0; 256 tokens, 4096 rows 158 507 118; 32768 tokens, 8192
+    // rows 16.4 23.1 16.6.
+    const int lg = fill.lg, id = (c * kBlock + tid) >> lg, groups = nc * (kBlock >> lg);
+    const int in = tid & ((1 << lg) - 1);
+    if (fill.share == 1) {
+      for (int e = id; e < E; e += groups)
+        for (int i = eoff[e + 1] - eoff[e] + in; i < C; i += 1 << lg)
+          row_src[(int64_t)e * C + i] = -1;
+    } else {
+      const int windows = groups / fill.share, first = id / fill.share;   // windows at a time
+      const int at = ((id - first * fill.share) << lg) + in, step = fill.share << lg;
+      for (int e = first; e < E && first < windows; e += windows)
+        for (int64_t i = eoff[e + 1] - eoff[e] + at; i < C; i += step)
+          row_src[(int64_t)e * C + i] = -1;
+    }
   } else {
     // Rows past the last routed slot have no source.
     for (int64_t i = n_total + (int64_t)c * kBlock + tid; i < T * k; i += (int64_t)nc * kBlock)
@@ -731,6 +738,16 @@ uint64_t sync_limit_ticks() {
   return cache[dev] = (uint64_t)khz * us / 1000u;
 }
 
+// The power of two that covers a window up to one wavefront; several of those
+// to a window where the grid has more of them than there are windows.
+WindowFill window_fill(int nc, int E, int C) {
+  int lg = 0;
+  while (lg < 6 && (1 << lg) < C) ++lg;
+  const int groups = nc * (kBlock >> lg), need = (int)(((int64_t)C + (1 << lg) - 1) >> lg);
+  const int share = groups / E < need ? groups / E : need;
+  return {lg, share > 1 ? share : 1};
+}
+
 template <int KW, bool FIXED>
 hipError_t launch_layout_kw(const int32_t* idx, int64_t T, int k, int E, int peer_L, int R, int C,
                             int32_t* expert_count, int32_t* expert_offset,
@@ -738,6 +755,7 @@ hipError_t launch_layout_kw(const int32_t* idx, int64_t T, int k, int E, int pee
                             int32_t* row_src, void* workspace, uint32_t* status,
                             hipStream_t stream) {
   const LayoutGeom g = layout_geom(T, E);
+  const WindowFill fill = FIXED ? window_fill(g.nc, E, C) : WindowFill{0, 1};
   char* ws = static_cast<char*>(workspace);
   int32_t* bound = reinterpret_cast<int32_t*>(ws);
   int32_t* counts = reinterpret_cast<int32_t*>(ws + g.counts_offset);
@@ -756,7 +774,7 @@ hipError_t launch_layout_kw(const int32_t* idx, int64_t T, int k, int E, int pee
     hipLaunchKernelGGL((layout_place_kernel<KW, kPlaceSingle, FIXED>), dim3(1), dim3(kBlock),
                        lds_place, stream, idx, T, k, E, peer_L, R, C, g.chunk_tokens, g.nc,
                        g.ncp, counts, expert_count, expert_offset, rank_count, rank_offset, pos,
-                       row_src, bound, tickets, status, gen, flags, (uint64_t)0);
+                       row_src, bound, tickets, status, gen, flags, (uint64_t)0, fill);
     return hipGetLastError();
   }
   const void* fused = reinterpret_cast<const void*>(&layout_place_kernel<KW, kPlaceFused, FIXED>);
@@ -764,7 +782,7 @@ hipError_t launch_layout_kw(const int32_t* idx, int64_t T, int k, int E, int pee
     hipLaunchKernelGGL((layout_place_kernel<KW, kPlaceFused, FIXED>), dim3(g.nc), dim3(kBlock),
                        lds_place, stream, idx, T, k, E, peer_L, R, C, g.chunk_tokens, g.nc,
                        g.ncp, counts, expert_count, expert_offset, rank_count, rank_offset, pos,
-                       row_src, bound, tickets, status, gen, flags, sync_limit_ticks());
+                       row_src, bound, tickets, status, gen, flags, sync_limit_ticks(), fill);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(layout_count_kernel<KW>, dim3(g.nc), dim3(kBlock), lds_count, stream,
@@ -775,7 +793,7 @@ hipError_t launch_layout_kw(const int32_t* idx, int64_t T, int k, int E, int pee
                      dim3(kBlock), lds_place, stream, idx, T, k, E, peer_L, R, C,
                      g.chunk_tokens, g.nc, g.ncp, counts, expert_count, expert_offset,
                      rank_count, rank_offset, pos, row_src, bound, tickets, status, gen, flags,
-                     (uint64_t)0);
+                     (uint64_t)0, fill);
   return hipGetLastError();
 }
 
