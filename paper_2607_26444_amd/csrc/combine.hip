@@ -10,7 +10,7 @@
 // touched once.
 //
 // Explicit splits (combine_kernel; moe_combine_ex with a policy, a wavefront
-// count or a trace): persistent wavefronts over the byte-balanced plan (wavefront g of W takes
+// count or a trace), and large batches of few narrow rows: persistent wavefronts over the byte-balanced plan (wavefront g of W takes
 // parts g, g + W, ... or claims them at run time).  Slot metadata for a batch
 // of 64/k tokens is resolved once, one slot per lane, and parked in LDS; for
 // each token the wavefront walks the output row in 1 KiB segments, the next

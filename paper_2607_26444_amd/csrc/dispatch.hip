@@ -1,7 +1,7 @@
 // Dispatch: copy each routed token row into its rank's receive region.
 //
-// Default split (dispatch_unit_kernel): the batch is cut into (token, 1 KiB
-// slice of its row) units, one wavefront each, launched in token order.  A
+// Default split (dispatch_unit_kernel): the batch is cut into (token, 1 or 2
+// KiB slice of its row) units, one wavefront each, launched in token order.  A
 // wavefront loads its slice once and stores it to the token's k destination
 // rows, so x is read exactly once, and the hardware hands units out as
 // wavefronts retire: every compute unit takes the next work when it is free,
@@ -12,9 +12,10 @@
 // the chip by its slices.
 //
 // Explicit splits (dispatch_kernel; moe_dispatch_ex with a policy, a
-// wavefront count or a trace): persistent wavefronts over the byte-balanced
-// plan (Section 6.2 with one memory tier, Appendix D third level).  moe_layout leaves MOE_PLAN_PARTS
-// contiguous token ranges of equal byte cost; wavefront g of W takes parts g,
+// wavefront count or a trace), and rows of less than a line: persistent
+// wavefronts over the byte-balanced plan (Section 6.2 with one memory tier,
+// Appendix D third level).  moe_layout leaves MOE_PLAN_PARTS contiguous token
+// ranges of equal byte cost; wavefront g of W takes parts g,
 // g + W, g + 2W, ... or claims parts in plan order at run time.  A wavefront
 // reads its token's whole row into registers and stores it to each of the k
 // destinations; slot metadata for a batch of 64/k tokens is loaded once, one
@@ -232,14 +233,14 @@ __device__ __forceinline__ void store16(void* p, u32x4 v) {
 // split below (us before -> after, GB/s of algorithmic bytes after):
 //   16384 x 14 KiB, k = 8, Zipf 1.2 routing   380 -> 361  (5860)
 //   16384 x 14 KiB, k = 8, uniform            401 -> 399  (5300)
-//   32768 x 8 KiB, k = 8, Zipf 1.5            445 -> 416  (5800)
-//   16384 x 8 KiB, k = 8, uniform             221 -> 218  (5540)
+//   32768 x 8 KiB, k = 8, Zipf 1.5            443 -> 411  (5870)
+//   16384 x 8 KiB, k = 8, uniform             221 -> 223  (5410)
 //   8192 x 14 KiB, k = 16, uniform            508 -> 398  (5020)
 //   4096 x 14 KiB, k = 8, uniform, x in HBM / cached   104 -> 101 / 92 -> 93
 //   16384 x 2 KiB, k = 8, uniform             58 -> 50  (6040)
 //   32768 x 512 B, k = 8                      36.5 -> 27.9  (5410)
 //   512 x 14 KiB, k = 8                       22.6 -> 12.7
-//   16384 x 7 KiB fp8, k = 8, Zipf            197 -> 190
+//   16384 x 7 KiB fp8, k = 8, uniform / Zipf  209 / 197 -> 205 / 195
 // Slower: batches with most slots unused, whose wavefronts are bound by their
 // metadata chain and, at 32768 x 14 KiB, by the launch of so many of them
 // (half of the slots unused 457 -> 503, nine tenths 190 -> 287; at 4096 tokens
@@ -406,7 +407,8 @@ hipError_t launch_unit_as(const DispatchArgs& a, int waves, int wpb, hipStream_t
 
 // Bytes of x and of the rows written that the 256 MiB Infinity Cache takes in:
 // up to here ordinary stores end in it, and beyond non-temporal ones are the
-// better choice; from kAbsorbedMin on they gain (below, a launch is too short).
+// better choice; from kAbsorbedMin on they gain (below, a launch is too short,
+// and a step of 777 x 4112 B, k = 6, 1 us longer for the write-back at its end).
 constexpr int64_t kAbsorbedMin = 96ll << 20, kAbsorbedMax = 300ll << 20;
 
 // How the units are launched.  What bounds a batch is, by size: launch latency
@@ -420,8 +422,9 @@ constexpr int64_t kAbsorbedMin = 96ll << 20, kAbsorbedMax = 300ll << 20;
 //    32.  Rows off the line take ordinary stores (rows that share a line meet
 //    in L2: 32768 x 528 B, k = 8: persistent 43, non-temporal 49, this 36), and so
 //    does every destination that starts inside a line.
-// 2. Batches that the Infinity Cache absorbs: ordinary stores, slices of 2
-//    KiB, workgroups of four, 24 wavefronts (32 for fewer than 4 rows a
+// 2. Batches that the Infinity Cache absorbs, and smaller ones of rows under 2
+//    KiB off the line (8192 x 1040 B, k = 8: 16 22 15): ordinary stores, slices
+//    of 2 KiB, workgroups of four, 24 wavefronts (32 for fewer than 4 rows a
 //    token and for rows off the line, whose lives are longer).  Against the
 //    persistent split and non-temporal 1 KiB units:
 //      16384 x 2 KiB, k = 8    57 / 64   58 / 54   50 / 51
@@ -432,47 +435,53 @@ constexpr int64_t kAbsorbedMin = 96ll << 20, kAbsorbedMax = 300ll << 20;
 //      8192 x 2 KiB fp8, k = 8 27 / 26   33 / 32   27 / 26
 //      4096 x 7 KiB fp8, k = 8 45 / 46   52 / 50   45 / 47
 //      4096 x 6752 B, k = 6    32 / 30   43 / 36   33 / 31
-// 3. Beyond: non-temporal 1 KiB units (2 KiB for one row a token, whose
-//    wavefronts hold least: 16384 x 14 KiB, k = 1: 91 / 81 -> 90 / 70).  About
-//    112 KiB of stores in flight per compute unit for 8 rows a token (14
-//    wavefronts), more wavefronts for fewer, in workgroups of two; fp8 rows,
-//    whose slice-0 wavefront lives longer, in workgroups of four (12
-//    wavefronts; 16384 x 4 KiB, k = 8: of one 131, of two 130, of four 118).
-//    k = 8, persistent / workgroups of one, 12 wavefronts /
-//    of two, 12 / of two, 14 / of two, 16:
+// 3. Other bf16 batches: non-temporal 1 KiB units (2 KiB for one row a token,
+//    whose wavefronts hold least: 16384 x 14 KiB, k = 1: 91 / 81 -> 90 / 70).
+//    About 112 KiB of stores in flight per compute unit for 8 rows a token (14
+//    wavefronts), more wavefronts for fewer, in workgroups of two.  k = 8,
+//    persistent / workgroups of one, 12 wavefronts / of two, 12 / of two, 14 /
+//    of two, 16:
 //      16384 x 14 KiB, uniform   399 408 390 398 407      Zipf  377 365 374 359 375
 //      16384 x 10 KiB, uniform   285 289 277 276 286
+//      16384 x 8 KiB, uniform    221 226 224 223 -        Zipf  216 209 216 208 -
 //      16384 x 4 KiB, uniform    121 113 113 110 113      Zipf  121 107 110 107 110
 //      4096 x 14 KiB, uniform    104 105 100 101 104      Zipf  98 95 97 94 95
 //      with x re-read from the caches, 16384 x 14 KiB  344 364 359 358 358
 //    k = 4, 14 KiB: persistent 231, 18 wavefronts 221, 14 237; k = 2: 145,
 //    32 130, 14 163; k = 16 (8192 tokens): 506, 14 394.
-//    fp8, k = 8, persistent / ordinary stores / this: 16384 x 7 KiB 207 203 207
-//    (x cached 208 204 192, Zipf 197 194 190), 32768 x 7 KiB 421 405 415.
 //    Rows off the line want every wavefront (16384 x 8240 B, k = 4, at 32 /
-//    20 / 12: 155 173 201), in workgroups of one (16384 x 8256 B, k = 8: 239, of
-//    two 249).
-// 4. ... but rows of 4 to 8 KiB with 8 or more destinations take ordinary
-//    stores: 16384 x 8 KiB over 256 uniform windows, persistent 221 / 222,
-//    non-temporal 225 / 204, this 217 / 219; Zipf 216, 208, 212; 32768
-//    tokens 451, 459, 440, and whole steps 904, 874, 850.
+//    20 / 12: 155 173 201), large batches of them in workgroups of one (16384 x
+//    8256 B, k = 8: 239, of two 249).
+// 4. fp8 rows, whose slice-0 wavefront lives longer, in workgroups of four (16384
+//    x 4 KiB, k = 8: of one 131, of two 130, of four 118): rows of more than 4
+//    KiB of an x that the Infinity Cache does not keep from the kernel that
+//    wrote it (over 64 MiB) with ordinary stores and 16 wavefronts, else
+//    non-temporal and 12.  k = 8, persistent / ordinary / non-temporal:
+//      16384 x 7 KiB, uniform    209 205 209   (x cached 207 203 194)
+//      16384 x 7 KiB, Zipf       197 195 192
+//      16384 x 5 KiB, uniform    163 150 154   (162 150 139), Zipf 159 146 142
+//      8192 x 7 KiB, uniform     111 107 110   (107 104 97), Zipf 103 100 97
+//      16384 x 4 KiB, uniform    126 125 118   (125 124 104)
+//      32768 x 7 KiB, uniform    425 414 417, Zipf 407 387 380
 template <bool SCALES>
 hipError_t launch_unit(const DispatchArgs& a, hipStream_t stream) {
   const int64_t rows = a.rows_hint > 0 ? a.rows_hint : a.k;   // pair rows: half the slots
-  const int64_t touched = a.tokens * a.row_bytes * (rows + 1);
+  const int64_t x_bytes = a.tokens * a.row_bytes, touched = x_bytes * (a.k + 1);
   const bool off_line = a.row_bytes % kLine != 0;
   if (a.row_bytes < kWaveBytes)
     return off_line ? launch_unit_as<SCALES, false, 1>(a, 32, kWavesPerBlock, stream)
                     : launch_unit_as<SCALES, true, 1, false>(a, 32, kWavesPerBlock, stream);
-  if (touched <= kAbsorbedMax && (touched >= kAbsorbedMin || off_line))
+  if (touched <= kAbsorbedMax &&
+      (touched >= kAbsorbedMin || (off_line && a.row_bytes < 2 * kWaveBytes)))
     return launch_unit_as<SCALES, false, 2>(a, rows < 4 || off_line ? 32 : 24, kWavesPerBlock,
                                             stream);
-  const int wpb = SCALES ? kWavesPerBlock : off_line ? 1 : 2;
+  const int waves = off_line ? 32 : rows < 8 ? (int)(48 / rows) + 6 : SCALES ? 12 : 14;
+  if (SCALES && rows >= 8 && a.row_bytes > 4 * kWaveBytes && x_bytes > (64ll << 20))
+    return launch_unit_as<SCALES, false, 1>(a, 16, kWavesPerBlock, stream);
+  const int wpb = SCALES ? kWavesPerBlock
+                  : !off_line ? 2
+                              : touched < kAbsorbedMin ? kWavesPerBlock : 1;
   if (rows == 1) return launch_unit_as<SCALES, true, 2>(a, 32, wpb, stream);
-  const int waves = off_line ? 32 : rows < 8 ? (int)(48 / rows) + 6 : 14;
-  if (!SCALES && rows >= 8 && !off_line && touched > kAbsorbedMax &&
-      a.row_bytes > 4 * kWaveBytes && a.row_bytes <= 8 * kWaveBytes)
-    return launch_unit_as<SCALES, false, 1>(a, waves, wpb, stream);
   return launch_unit_as<SCALES, true, 1>(a, waves, wpb, stream);
 }
 

@@ -170,7 +170,8 @@ struct DispatchArgs {
 };
 
 // MOE_POLICY_BALANCED without a wavefront count or a trace takes the unit
-// kernel, everything else the explicit splits.
+// kernel (rows of less than a line: static parts), everything else the explicit
+// splits.
 hipError_t launch_dispatch(const DispatchArgs& a, int policy, hipStream_t stream);
 
 struct CombineArgs {
@@ -195,7 +196,8 @@ struct CombineArgs {
 };
 
 // MOE_POLICY_BALANCED without a wavefront count or a trace takes the unit
-// kernel, everything else the explicit splits.
+// kernel (large batches of few narrow rows: static parts), everything else the
+// explicit splits.
 hipError_t launch_combine(const CombineArgs& a, int policy, hipStream_t stream);
 
 struct ExpertArgs {

@@ -5,8 +5,9 @@ tensors and the current HIP stream to the C entry point of the same name;
 all work runs in the library's kernels.  The calls of a batch go through the
 native marshalling of csrc/pycall.cpp, the others through ctypes.  torch is
 imported before the library is loaded so that both use the one HIP runtime
-already in the process.  There is no fallback: without libmoe.so every call raises, and
-without a _moecall built for the running interpreter every call of a batch.
+already in the process.  There is no fallback: without libmoe.so every call
+raises, and without a _moecall built for the running interpreter every call of
+a batch.
 """
 from __future__ import annotations
 
