@@ -10,14 +10,15 @@
 // touched once.
 //
 // Explicit splits (combine_kernel; moe_combine_ex with a policy, a wavefront
-// count or a trace), and large batches of few narrow rows: persistent wavefronts over the byte-balanced plan (wavefront g of W takes
-// parts g, g + W, ... or claims them at run time).  Slot metadata for a batch
-// of 64/k tokens is resolved once, one slot per lane, and parked in LDS; for
-// each token the wavefront walks the output row in 1 KiB segments, the next
-// segment's gathers issued before the current one is reduced.  Output rows of
-// 8-16 KiB are kept in registers and stored as one burst per token.  Unused
-// and capacity-dropped slots are redirected to a routed row of the same
-// token, their data is zeroed bitwise and their weight is 0 (a plain multiply
+// count or a trace), and large batches of few narrow rows: persistent
+// wavefronts over the byte-balanced plan (wavefront g of W takes parts g,
+// g + W, ... or claims them at run time).  Slot metadata for a batch of 64/k
+// tokens is resolved once, one slot per lane, and parked in LDS; for each token
+// the wavefront walks the output row in 1 KiB segments, the next segment's
+// gathers issued before the current one is reduced.  Output rows of 8-16 KiB
+// are kept in registers and stored as one burst per token.  Unused and
+// capacity-dropped slots are redirected to a routed row of the same token,
+// their data is zeroed bitwise and their weight is 0 (a plain multiply
 // by 0 would turn an Inf in that row into NaN).
 
 #include "moe_internal.h"
